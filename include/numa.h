@@ -375,7 +375,7 @@ int32_t numa_stage_rhs(numa_mesh_t m, int32_t prec, const double *q, double *r, 
  * state: they are factored (band LU, in one workgroup per line) into the
  * workspace at the first call and whenever dt changes, so the workspace must
  * be attached with NUMA_WS_IMEX (NUMA_ENOMEM otherwise); each step then solves
- * all lines with one lane per line.  The mesh's filter and integrator settings
+ * all lines, one lane per line and element layer.  The mesh's filter and integrator settings
  * are not used.  Uses the workspace scratch like numa_step.  To start, pass
  * qprev = qcur (a forward first step) or a state one step back. */
 int32_t numa_imex_step(numa_mesh_t m, int32_t prec, double dt, double ra, int32_t nsteps, double *qprev,

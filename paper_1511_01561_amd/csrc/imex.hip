@@ -28,10 +28,12 @@
 // (wall rows: w = r_w), a band matrix of half-width 2N that depends on dt and
 // the reference state only.  It is factored once per dt (LU without pivoting:
 // I plus dt^2 times a vertical acoustic operator) into the workspace; every
-// step then streams each line bottom to top and back, one lane per line, so
-// that neighbouring lanes read neighbouring lattice lines (coalesced).  The
+// step then solves each line bottom to top and back; neighbouring lanes hold
+// neighbouring lattice lines (coalesced).  The
 // new velocity is the explicit one with its n component replaced.
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace numa {
 namespace {
@@ -230,7 +232,8 @@ __device__ __forceinline__ double gat(double w0, double wN, int e, int k, double
     return dk / hk;
 }
 
-// One step's vertical correction: one lane per line, four passes along it;
+// One step's vertical correction of lines too tall for k_imex_lines (below):
+// one lane per line, four passes along it;
 // an element's N+1 nodes at a time, node e N + N finishing with element e + 1
 // (or as the top wall node).
 template <int N, bool SHELL>
@@ -411,6 +414,299 @@ __global__ __launch_bounds__(256) void k_imex_solve(ImexArgs a)
     }
 }
 
+// One step's vertical correction with the work of a line spread over lanes: a
+// workgroup takes kLines lines and one lane per (line, element layer), so the
+// explicit parts of the correction (everything but the band solve, which is
+// a recurrence along the line) run for all layers at once.  kLines = 16 lines
+// of 8 bytes fill a 128-byte cache line.  Element derivatives meet at the
+// layer interfaces through LDS; the right side of the band system and its
+// solution stay in LDS (X), the line's other values in the lanes' registers, so
+// that every state value, reference value and factor is read once.  Per unique
+// node (box) 34 doubles are read and 10 written, so the kernel is bound by
+// memory: 32x32x16, N = 4 (1.06 M nodes, 16,384 lines, 375 MB) 372 -> 84 us,
+// 4.5 TB/s, against one lane per line over the whole kernel (k_imex_solve:
+// 64 workgroups there, each value's loads behind the level before it).
+constexpr int kLines = 16;
+constexpr int kChunk = 8;  // levels of factors staged in LDS at a time
+
+template <int N>
+constexpr int solve_stage() { return kChunk * (2 * N + 1) * kLines; }
+
+inline int imex_pad_levels(int nk) { return (nk + kChunk - 1) / kChunk * kChunk; }
+
+// LDS of k_imex_lines: X, three interface exchanges, the staged factors
+template <int N>
+size_t imex_lines_lds(int nk)
+{
+    const int nz = (nk - 1) / N;
+    return 8 * ((size_t)kLines * (imex_pad_levels(nk) + 3 * nz) + solve_stage<N>());
+}
+
+// L y = x, then U w = y, on the workgroup's lines by its first wavefront: the
+// four 16-lane groups load two levels of factors each (kChunk levels in all, a
+// chunk ahead of the recurrence, through registers into F) and run the
+// recurrence alike.  The newest value enters last, so a level waits for
+// one multiply-add of the level before it.
+template <int N>
+__device__ __forceinline__ void band_solve(const double *lu, int64_t nh, int64_t L, int nk, double *X, double *F,
+                                           int line, int grp)
+{
+    constexpr int B = 2 * N, W = 2 * B + 1, H = kChunk / 4;
+    const int nch = (nk + kChunk - 1) / kChunk;
+    double pf[H * (B + 1)], h[B];
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+    };
+    // factors of chunk c: d = 0..B-1 (L) or B..2B (1/U_gg, U)
+    auto load = [&](int c, auto upper) {
+        constexpr int D0 = decltype(upper)::value ? B : 0, M = decltype(upper)::value ? B + 1 : B;
+#pragma unroll
+        for (int r = 0; r < H; ++r) {
+            const int g = c * kChunk + grp + 4 * r;
+            const double *p = lu + ((int64_t)g * W + D0) * nh + L;
+#pragma unroll
+            for (int d = 0; d < M; ++d) pf[r * M + d] = g < nk ? p[d * nh] : 0.0;
+        }
+    };
+    auto stage = [&](auto upper) {
+        constexpr int M = decltype(upper)::value ? B + 1 : B;
+        wave_sync();  // the chunk before has been read
+#pragma unroll
+        for (int r = 0; r < H; ++r)
+#pragma unroll
+            for (int d = 0; d < M; ++d) F[((grp + 4 * r) * M + d) * kLines + line] = pf[r * M + d];
+        wave_sync();
+    };
+    using Lo = std::integral_constant<bool, false>;
+    using Up = std::integral_constant<bool, true>;
+#pragma unroll
+    for (int s = 0; s < B; ++s) h[s] = 0.0;
+    load(0, Lo{});
+    for (int c = 0; c < nch; ++c) {
+        stage(Lo{});
+        if (c + 1 < nch) load(c + 1, Lo{});
+        else load(c, Up{});
+#pragma unroll
+        for (int l = 0; l < kChunk; ++l) {
+            double y = X[(c * kChunk + l) * kLines + line];
+#pragma unroll
+            for (int s = B; s >= 1; --s) y = fma(-F[(l * B + B - s) * kLines + line], h[s - 1], y);
+#pragma unroll
+            for (int s = B - 1; s > 0; --s) h[s] = h[s - 1];
+            h[0] = y;
+            X[(c * kChunk + l) * kLines + line] = y;
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < B; ++s) h[s] = 0.0;
+    for (int c = nch - 1; c >= 0; --c) {
+        stage(Up{});
+        if (c > 0) load(c - 1, Up{});
+#pragma unroll
+        for (int l = kChunk - 1; l >= 0; --l) {
+            double w = X[(c * kChunk + l) * kLines + line];
+#pragma unroll
+            for (int s = B; s >= 1; --s) w = fma(-F[(l * (B + 1) + s) * kLines + line], h[s - 1], w);
+            w *= F[l * (B + 1) * kLines + line];  // beyond the line: zero
+#pragma unroll
+            for (int s = B - 1; s > 0; --s) h[s] = h[s - 1];
+            h[0] = w;
+            X[(c * kChunk + l) * kLines + line] = w;
+        }
+    }
+}
+
+// D f on one element's nodes (the zeta derivative)
+template <int N>
+__device__ __forceinline__ void derive(const ImexArgs &a, const double (&f)[N + 1], double (&df)[N + 1])
+{
+    constexpr int P = N + 1;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        double s = 0.0;
+#pragma unroll
+        for (int m = 0; m < P; ++m) s = fma(a.D[k * P + m], f[m], s);
+        df[k] = s;
+    }
+}
+
+template <int N, bool SHELL, int MAXT>
+__global__ __launch_bounds__(MAXT) void k_imex_lines(ImexArgs a)
+{
+    constexpr int P = N + 1;
+    extern __shared__ double sm[];
+    const int nk = a.nk, nz = (nk - 1) / N, nkp = (nk + kChunk - 1) / kChunk * kChunk;
+    double *X = sm, *E0 = X + nkp * kLines, *E1 = E0 + nz * kLines, *E2 = E1 + nz * kLines, *F = E2 + nz * kLines;
+    const int t = threadIdx.x, line = t % kLines, e = t / kLines;
+    const int64_t nh = a.nh, nu = a.nu;
+    int64_t L = (int64_t)blockIdx.x * kLines + line;
+    const bool mine = L < nh;  // lanes past the last line repeat it and write nothing
+    if (!mine) L = nh - 1;
+    const bool act = e < nz;
+    const LineGeo lg = line_geo<N>(a, L);
+    const double n0 = SHELL ? lg.n[0] : 0.0, n1 = SHELL ? lg.n[1] : 0.0, n2 = SHELL ? lg.n[2] : 1.0;
+    const double dt = a.dt, ra = a.ra, w0 = a.w[0], wN = a.w[N];
+    const int top = e == nz - 1 ? P : N;  // nodes the lane owns: k < top
+    const int64_t I0 = L + nh * ((int64_t)e * N);
+    const int x0 = e * N * kLines + line;
+    for (int g = nk + e; g < nkp; g += (int)(blockDim.x / kLines)) X[g * kLines + line] = 0.0;
+    // shared by the phases: rho_bar, c2, kap at the nodes; G at an owned node
+    // k is (d_k + the derivative of the layer below at k = 0) times gi[k], times
+    // w_0 at an interface
+    double rb[P], cc[P], kp[P], sv[P], gn[P], gi[P];
+    auto gat = [&](int k, double dk, const double *Ex) {
+        if (k == 0 && e > 0) return (wN * Ex[(e - 1) * kLines + line] + w0 * dk) * gi[0];
+        return dk * gi[k];
+    };
+    double rr[P], rt[P], be[P], sd0[P], swv[P], rw[P], t0[P], tw[P];
+    double df[P], dh[P], dtb[P];
+    if (act) {
+        double f[P], h[P], tb[P];
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            const int64_t I = I0 + nh * k;
+            rb[k] = a.ref[I];
+            tb[k] = SHELL ? a.ref[nu + I] : a.theta0;
+            cc[k] = a.gamma * a.ref[2 * nu + I] / rb[k];
+            kp[k] = cc[k] * rb[k] / tb[k];
+            const double c0 = a.qcur[I], p0 = a.qprev[I], c4 = a.qcur[4 * nu + I], p4 = a.qprev[4 * nu + I];
+            const double c3 = a.qcur[3 * nu + I], p3 = a.qprev[3 * nu + I];
+            sd0[k] = 2.0 * c0 - p0;
+            if (SHELL) {
+                swv[k] = n0 * (2.0 * a.qcur[nu + I] - a.qprev[nu + I]) +
+                         n1 * (2.0 * a.qcur[2 * nu + I] - a.qprev[2 * nu + I]) + n2 * (2.0 * c3 - p3);
+                const double *sl = a.slay + 4 * (e * P + k);
+                sv[k] = 1.0 / (sl[0] * sl[0]);
+                gn[k] = -sl[3];
+                gi[k] = sl[1];
+            } else {
+                swv[k] = 2.0 * c3 - p3;
+                sv[k] = 1.0;
+                gn[k] = a.gz;
+                gi[k] = lg.izz;
+                // Robert-Asselin: q + ra (q_prev - 2 q + q_new) with the new value added at the end
+                t0[k] = fma(ra, p0 - 2.0 * c0, c0);
+                tw[k] = fma(ra, p3 - 2.0 * c3, c3);
+            }
+            f[k] = sv[k] * rb[k] * swv[k];
+            h[k] = cc[k] * sd0[k] + kp[k] * (2.0 * c4 - p4);
+        }
+        if (e > 0)  // the mean of two layers
+            gi[0] = SHELL ? 1.0 / (wN / a.slay[4 * ((e - 1) * P + N) + 1] + w0 / gi[0]) : lg.izz / (wN + w0);
+        derive<N>(a, f, df);
+        derive<N>(a, h, dh);
+        E0[t] = df[N];
+        E1[t] = dh[N];
+        if (SHELL) {
+            derive<N>(a, tb, dtb);
+            E2[t] = dtb[N];
+        }
+    }
+    __syncthreads();
+    double rho_a = 0.0, rt_a = 0.0;  // r_rho and r_theta of the layer's top node
+    if (act) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            if (k >= top) continue;
+            const int64_t I = I0 + nh * k;
+            const int g = e * N + k;
+            const double gf = gat(k, df[k], E0), gh = gat(k, dh[k], E1);
+            rr[k] = a.qs[I] + dt * gf / sv[k];
+            const double qw = SHELL ? n0 * a.qs[nu + I] + n1 * a.qs[2 * nu + I] + n2 * a.qs[3 * nu + I]
+                                    : a.qs[3 * nu + I];
+            rw[k] = g == 0 || g == nk - 1 ? qw : qw + dt * (gh - gn[k] * sd0[k]) / rb[k];
+            rt[k] = a.qs[4 * nu + I];
+            if (SHELL) {
+                be[k] = gat(k, dtb[k], E2);
+                rt[k] += dt * be[k] * swv[k];
+            }
+        }
+    }
+    __syncthreads();  // the exchanges are read: E0, E1 carry the interface values downwards
+    if (act) {
+        E0[t] = rr[0];
+        E1[t] = rt[0];
+        if (!SHELL && mine) {  // u, v and theta of the box are the explicit step's
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                if (k >= top) continue;
+#pragma unroll
+                for (int v = 1; v < 5; v += v == 2 ? 2 : 1) {
+                    const int64_t J = v * nu + I0 + nh * k;
+                    const double vc = a.qcur[J], vp = a.qprev[J], nv = v == 4 ? rt[k] : a.qs[J];
+                    a.qprev[J] = vc + ra * (vp - 2.0 * vc + nv);
+                    a.qcur[J] = nv;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (act) {
+        double h[P];
+        if (top == N) {
+            rho_a = E0[t + kLines];
+            rt_a = E1[t + kLines];
+        }
+#pragma unroll
+        for (int k = 0; k < P; ++k)
+            h[k] = k < N || top == P ? cc[k] * rr[k] + kp[k] * rt[k] : cc[k] * rho_a + kp[k] * rt_a;
+        derive<N>(a, h, dh);
+        E2[t] = dh[N];
+    }
+    __syncthreads();
+    if (act)
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            if (k >= top) continue;
+            const int g = e * N + k;
+            const double gh = gat(k, dh[k], E2);
+            X[x0 + k * kLines] = g == 0 || g == nk - 1 ? rw[k] : rw[k] - dt * (gh - gn[k] * rr[k]) / rb[k];
+        }
+    __syncthreads();
+    if (t < 64) band_solve<N>(a.lu, nh, L, nk, X, F, line, t / kLines);
+    __syncthreads();
+    // rho' = r_rho - (dt/s) G(s rho_bar w), theta' = r_theta - dt beta w, the
+    // velocity's n component replaced by w; the filtered q^n
+    double wv[P];
+    if (act) {
+        double f[P];
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            wv[k] = X[x0 + k * kLines];
+            f[k] = sv[k] * rb[k] * wv[k];
+        }
+        derive<N>(a, f, df);
+        E0[t] = df[N];
+    }
+    __syncthreads();
+    if (act && mine)
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            if (k >= top) continue;
+            const int64_t I = I0 + nh * k;
+            const double gf = gat(k, df[k], E0), w = wv[k];
+            const double nr = rr[k] - dt * gf / sv[k];
+            if (SHELL) {
+                const double u0 = a.qs[nu + I], u1 = a.qs[2 * nu + I], u2 = a.qs[3 * nu + I];
+                const double qw = n0 * u0 + n1 * u1 + n2 * u2;
+                const double nv[5] = {nr, u0 - qw * n0 + w * n0, u1 - qw * n1 + w * n1, u2 - qw * n2 + w * n2,
+                                      rt[k] - dt * be[k] * w};
+#pragma unroll
+                for (int v = 0; v < 5; ++v) {
+                    const double vc = a.qcur[v * nu + I], vp = a.qprev[v * nu + I];
+                    a.qprev[v * nu + I] = vc + ra * (vp - 2.0 * vc + nv[v]);
+                    a.qcur[v * nu + I] = nv[v];
+                }
+            } else {
+                a.qprev[I] = fma(ra, nr, t0[k]);
+                a.qcur[I] = nr;
+                a.qprev[3 * nu + I] = fma(ra, w, tw[k]);
+                a.qcur[3 * nu + I] = w;
+            }
+        }
+}
+
 ImexArgs imex_args(Mesh &m, double dt, double ra, double *qprev, double *qcur)
 {
     ImexArgs a{};
@@ -442,12 +738,31 @@ ImexArgs imex_args(Mesh &m, double dt, double ra, double *qprev, double *qcur)
     return a;
 }
 
+// A lane per (line, element layer): up to 32 layers, 512 lanes, the most that
+// leaves a lane 256 registers (N = 5, 20 layers at 32x32: step 897 -> 588 us,
+// N = 6, 24 layers at 16x16: 1,079 -> 362 us); taller lines keep one lane per
+// line.
+template <int N>
+bool imex_lines_ok(int nk) { return (nk - 1) / N * kLines <= 512 && imex_lines_lds<N>(nk) <= 65536; }
+
 template <int N>
 int32_t launch_imex_n(const ImexArgs &a, bool factor, size_t lds, hipStream_t s)
 {
     if (factor)
         hipLaunchKernelGGL((k_imex_factor<N>), dim3((unsigned)a.nh), dim3(64), lds, s, a);
-    else if (a.shell)
+    else if (imex_lines_ok<N>(a.nk)) {
+        const int nz = (a.nk - 1) / N, bt = nz < 4 ? 64 : (nz * kLines + 63) / 64 * 64;
+        const dim3 grid((unsigned)((a.nh + kLines - 1) / kLines)), block(bt);
+        const size_t ldsl = imex_lines_lds<N>(a.nk);
+        if (a.shell && bt <= 256)
+            hipLaunchKernelGGL((k_imex_lines<N, true, 256>), grid, block, ldsl, s, a);
+        else if (a.shell)
+            hipLaunchKernelGGL((k_imex_lines<N, true, 512>), grid, block, ldsl, s, a);
+        else if (bt <= 256)
+            hipLaunchKernelGGL((k_imex_lines<N, false, 256>), grid, block, ldsl, s, a);
+        else
+            hipLaunchKernelGGL((k_imex_lines<N, false, 512>), grid, block, ldsl, s, a);
+    } else if (a.shell)
         hipLaunchKernelGGL((k_imex_solve<N, true>), dim3((unsigned)((a.nh + 255) / 256)), dim3(256), 0, s, a);
     else
         hipLaunchKernelGGL((k_imex_solve<N, false>), dim3((unsigned)((a.nh + 255) / 256)), dim3(256), 0, s, a);

@@ -61,6 +61,35 @@ def test_imex_parity_generic_box_path(torch_cuda, oracle_mod, ne):
     assert_groups(ga, oa, TOL64, "imex generic filtered ne=%s" % (ne,))
 
 
+@pytest.mark.parametrize("N,nz", [(4, 1), (1, 2), (8, 5), (3, 15), (3, 16), (5, 17), (3, 32), (3, 33)])
+def test_imex_line_layouts(torch_cuda, oracle_mod, N, nz):
+    """Layers per workgroup of the line kernel: fewer lanes than a wavefront,
+    one and two block sizes, its last layer count and the one-lane-per-line
+    kernel beyond it; level counts that do and do not fill a chunk of factors;
+    line counts (nh) that leave a workgroup partly empty."""
+    wl = inputs.box_workload(4, 3, nz, N, 12e3, 9e3, 600.0 * nz, terrain=200.0,
+                             bubble_centre=(6e3, 4.5e3, 300.0 * nz), bubble_radius=2.5e3)
+    p = Pair_(wl, oracle_mod)
+    _, (oa, ob), (ga, gb) = imex_case(p, 0.05, 0.05, 2, 40 + nz)
+    assert_groups(gb, ob, TOL64, "imex q^{n+1} N=%d nz=%d" % (N, nz))
+    assert_groups(ga, oa, TOL64, "imex filtered q^n N=%d nz=%d" % (N, nz))
+
+
+@pytest.mark.parametrize("nz", [1, 17, 33])
+def test_imex_line_layouts_shell(torch_cuda, oracle_mod, nz):
+    """The same on radial lines, from a random state: its rho' right-hand
+    side is no nearly cancelled sum, so the plain bound applies (on tall
+    lines the balanced jet's rho' separates by ~1e-12 through the rounding of
+    the metric in the explicit stage alone)."""
+    p = Pair_(inputs.shell_workload(2, nz, 2, 0, H=0.8e3 * nz), oracle_mod)
+    qm, q0 = (inputs.random_state(p.nu, 60 + k) for k in (0, 1))
+    oa, ob = p.o.imex_step(qm, q0, 0.2, 0.05, 2)
+    ga, gb = p.dev(qm), p.dev(q0)
+    p.g.imex_step(ga, gb, 0.2, 0.05, 2)
+    assert_groups(p.host(gb), ob, TOL64, "shell imex q^{n+1} nz=%d" % nz)
+    assert_groups(p.host(ga), oa, TOL64, "shell imex filtered q^n nz=%d" % nz)
+
+
 def test_imex_forward_start_and_no_filter(torch_cuda, oracle_mod):
     """qprev = qcur (a forward first step), ra = 0."""
     p = Pair_(inputs.small_box(), oracle_mod)
