@@ -57,7 +57,7 @@ extern "C" {
 #define NUMA_STAGE_BLOCK 1   /* one kernel per block of element columns sums the copies in LDS */
 #define NUMA_STAGE_COLOUR 2  /* 8 colour passes add J w R into a unique-node accumulator */
 #define NUMA_STAGE_SPLIT 3   /* element kernel finishes its run's interior nodes; a face kernel the rest */
-#define NUMA_STAGE_AUTO 4    /* default: NUMA_STAGE_SPLIT in FP64 where it applies, else NUMA_STAGE_GATHER */
+#define NUMA_STAGE_AUTO 4    /* default: by precision and size, see numa_mesh_set_stage */
 
 #define NUMA_RK_SSP33 0      /* three-stage third-order SSP Runge-Kutta (Shu-Osher) */
 #define NUMA_RK_SSP53 1      /* five-stage third-order SSP Runge-Kutta (Spiteri-Ruuth) */
@@ -227,9 +227,11 @@ int32_t numa_mesh_set_metric(numa_mesh_t m, int32_t mode);
  *   64, 28, 16, 10, 7, 5, 4, 2 elements), mixed precision N <= 4; the stage
  *   may write its input state (the nodes the element kernel finishes are
  *   read by no other workgroup).
- * NUMA_STAGE_AUTO (default): NUMA_STAGE_SPLIT for FP64 stages where it
- *   applies, NUMA_STAGE_GATHER otherwise (the faster of the two in each
- *   precision on the 64 x 64 x 16 box, N = 3..8).
+ * NUMA_STAGE_AUTO (default): what was measured fastest for the precision and
+ *   the element-local nodes of the launch (for a batch, of its NUMA_STAGE_AUTO
+ *   items together): the gather with one node per lane for small launches, then
+ *   NUMA_STAGE_SPLIT for FP64 stages where it applies (N <= 3: the column gather
+ *   in between), else NUMA_STAGE_GATHER.  These give the same state bit for bit.
  * Meshes or stages a mode does not cover run NUMA_STAGE_GATHER.  NUMA_EINVAL
  * for an unknown mode.  Host only. */
 int32_t numa_mesh_set_stage(numa_mesh_t m, int32_t mode);
@@ -311,7 +313,7 @@ int32_t numa_rk_stage(numa_mesh_t m, int32_t stage, double dt, const double *qn,
  * update (the mesh's DSS schedule, numa_mesh_set_stage: by default in FP64
  * on the box the element kernel already sums the copies inside its run of
  * elements and finishes those nodes, and writes only the others' copies for
- * the finish kernel).  In FP64 (box and shell; not the generic box path, nor the box at
+ * the finish kernel).  In FP64 (box and shell; not NUMA_STAGE_GATHER on the box at
  * N = 5, 6 with the recomputed metric) the contribution
  * away from the walls is J w (q_s + c dt R), so that the finish need not read
  * q_s there; with the recomputed metric M is then the sum of the recomputed

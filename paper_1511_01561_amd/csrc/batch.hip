@@ -17,6 +17,11 @@ using namespace dev;
 
 constexpr int kMaxBatch = 16;  // items per launch (kernel-argument table)
 
+// How the items of a launch run a stage: the gather DSS with the element
+// kernel of the order and precision, the colour passes, the split DSS, or the
+// gather DSS with one node per lane (small launches)
+enum { kGather = 0, kColour = 1, kSplit = 2, kNode = 3 };
+
 struct BatchItem {
     const double *qs;  // stage input state [5][nu]
     double *qout;      // stage output state
@@ -52,6 +57,39 @@ struct Batch {
     BatchItem it[kMaxBatch];
 };
 static_assert(sizeof(Batch) <= 4096, "the batch table must fit the kernel arguments");
+
+// The gather of a column kernel: calls f(k, q, rho_bar, x, p') for the nodes
+// k = 0..P-1 of the column based at unique node `base` (levels `layer` apart,
+// wrapping at nk), G nodes' loads in flight together; G below P where the
+// registers of more do not pay.
+template <int P, int G, typename T, typename F>
+__device__ __forceinline__ void gather_column(const RhsArgs<T> &a, double theta0, int base, int layer, int gk0, F f)
+{
+#pragma unroll
+    for (int k0 = 0; k0 < P; k0 += G) {
+        const int n = P - k0 < G ? P - k0 : G;
+        double q[G][5], rb[G], pb[G], x[G], pp[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            if (k >= n) continue;
+            int gk = gk0 + k0 + k;
+            if (gk == a.nk) gk = 0;
+            const int32_t I = base + layer * gk;
+            const double *qp = a.q + I, *rf = a.ref + I;
+#pragma unroll
+            for (int v = 0; v < 5; ++v) q[k][v] = qp[v * a.nu];
+            rb[k] = rf[0];
+            pb[k] = rf[2 * a.nu];
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            if (k < n) x[k] = box_eos_x(q[k][0], q[k][4], rb[k], theta0);
+        eos_nodes<G>(n, x, pb, a.gamma, a.eos, pp);
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            if (k < n) f(k0 + k, q[k], rb[k], pp[k]);
+    }
+}
 
 // item of launch-wide block g (items are in ascending eoff / boff order)
 __device__ __forceinline__ int batch_item(const Batch &B, int g, bool fin)
@@ -115,9 +153,11 @@ __device__ __forceinline__ void store_contributions(const BatchItem &it, int e, 
     }
 }
 
-// One workgroup per element (the launch-wide element index, XCD-remapped).
+// One workgroup per element (the launch-wide element index, XCD-remapped).  At
+// N = 8 a workgroup is three wavefronts on each SIMD: in FP32 the registers are
+// held to six, two workgroups (one more register costs a workgroup).
 template <int N, typename T, int GEO>
-__global__ __launch_bounds__(block_threads<N>()) void k_elem_batch(Batch B)
+__global__ __launch_bounds__(block_threads<N>(), N == 8 && sizeof(T) == 4 ? 6 : 1) void k_elem_batch(Batch B)
 {
     constexpr int NP = (N + 1) * (N + 1) * (N + 1);
     __shared__ T s[8][NP];
@@ -127,21 +167,15 @@ __global__ __launch_bounds__(block_threads<N>()) void k_elem_batch(Batch B)
     const RhsArgs<T> a = elem_args<T>(B, it);
     NodeOut<T> o;
     const int l = threadIdx.x;
+    const bool act = l < NP;
     // element_rhs, with the node's state kept for the fold
     NodeIn<T> in;
     node_gather<N, T, false, GEO>(a, e, l, in);
+    T Di[N + 1], Dj[N + 1], Dk[N + 1];
+    if (act) d_rows<N, T>(a.D, l, Di, Dj, Dk);  // in flight with the gather
     node_stage<N, T, false, GEO>(a, e, l, in, s);
     __syncthreads();
-    const bool act = l < NP;
-    if (act) {
-        if constexpr (GEO == kMetricBox) {  // FP64 at N = 7, 8: R direction by direction
-            node_derive_box_dirs<N, T>(a, l, in, s, o);
-        } else {
-            T Di[N + 1], Dj[N + 1], Dk[N + 1];
-            d_rows<N, T>(a.D, l, Di, Dj, Dk);
-            node_derive<N, T, false, GEO>(a, l, in, Di, Dj, Dk, s, o);
-        }
-    }
+    if (act) node_derive<N, T, false, GEO>(a, l, in, Di, Dj, Dk, s, o);
     __syncthreads();  // every lane has finished reading the tile
     T *st = &s[0][0];
     if (act) {
@@ -193,6 +227,10 @@ template <int N> constexpr int split_eb()
 }
 template <int N> constexpr int split_threads() { return ((split_eb<N>() * (N + 1) * (N + 1) + 63) / 64) * 64; }
 
+// nodes gathered together: the column, or in the streaming kernel as many as
+// its occupancy allows
+template <int N, typename T> constexpr int col_group() { return N == 4 && sizeof(T) == 4 ? 3 : N + 1; }
+template <int N, typename T> constexpr int stream_group() { return N <= 6 ? 4 : 5; }
 template <int N, typename T, int MODE = 0>
 constexpr int col_blocks() { return (sizeof(T) == 4 && N == 4) ? 4 : 1; }
 
@@ -376,9 +414,9 @@ __device__ __forceinline__ void split_store(const BatchItem &it, const SplitGeo 
             double r[5], o[5];
 #pragma unroll
             for (int v = 0; v < 5; ++v) {
-                r[v] = (double)st[(qq * NP + l) * 5 + v];
-                if (ii == 0) r[v] += (double)st[((qq - 1) * NP + lw) * 5 + v];
-                r[v] *= pf.m[p];
+                T c = st[(qq * NP + l) * 5 + v];
+                if (ii == 0) c += st[((qq - 1) * NP + lw) * 5 + v];
+                r[v] = (double)c * pf.m[p];
             }
             if (fold) {
 #pragma unroll
@@ -420,6 +458,12 @@ __global__ __launch_bounds__((col_threads<N, T>()), (col_blocks<N, T, MODE>())) 
     double c0 = 0.0, c1 = 0.0, c2 = 0.0, c3 = 0.0;
     int ez = 0, base = 0;
     const int layer = a.ni * a.nj;
+    T Di[P], Dj[P];
+#pragma unroll
+    for (int m = 0; m < P; ++m) {
+        Di[m] = a.D[i * P + m];
+        Dj[m] = a.D[j * P + m];
+    }
     if (act) {
         BoxElem be;
         if constexpr (MODE == 1) {
@@ -441,52 +485,32 @@ __global__ __launch_bounds__((col_threads<N, T>()), (col_blocks<N, T, MODE>())) 
         if (gj == a.nj) gj = 0;
         base = gi + a.ni * gj;
         T col[8][P];
+        gather_column<P, col_group<N, T>()>(a, it.theta0, base, layer, be.ez * N,
+                                            [&](int k, const double *qv, double rb, double pp) {
+                                                const double rho = rb + qv[0], ir = 1.0 / rho;
+                                                irho[k] = (T)ir;
+                                                buoy[k] = F64 ? (T)qv[0] : (T)(qv[0] * ir);
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-            int gk = be.ez * N + k;
-            if (gk == a.nk) gk = 0;
-            const int32_t I = base + layer * gk;
-            const double *qp = a.q + I, *rf = a.ref + I;
-            const double rp = qp[0], u = qp[a.nu], v = qp[2 * a.nu], w = qp[3 * a.nu], tp = qp[4 * a.nu];
-            const double rb = rf[0], tb = it.theta0, pb = rf[2 * a.nu];
-            const double rho = rb + rp;
-            // p' = p_bar ((rho theta / rho_bar theta_bar)^gamma - 1) without cancellation
-            const double dl = rp * tb + rb * tp + rp * tp;
-            const double pp = pb * eos_rel(dl / (rb * tb), a.gamma, a.eos);
-            const double ir = 1.0 / rho;
-            irho[k] = (T)ir;
-            buoy[k] = F64 ? (T)rp : (T)(rp * ir);
-            col[0][k] = (T)(rho * u);
-            col[1][k] = (T)(rho * v);
-            col[2][k] = (T)(rho * w);
-            col[3][k] = (T)u;
-            col[4][k] = (T)v;
-            col[5][k] = (T)w;
-            col[6][k] = (T)tp;
-            col[7][k] = (T)pp;
+                                                for (int v = 0; v < 3; ++v) {
+                                                    col[v][k] = (T)(rho * qv[1 + v]);
+                                                    col[3 + v][k] = (T)qv[1 + v];
+                                                }
+                                                col[6][k] = (T)qv[4];
+                                                col[7][k] = (T)pp;
 #pragma unroll
-            for (int f = 0; f < 8; ++f) s[q][f][c + PP * k] = col[f][k];
-        }
+                                                for (int f = 0; f < 8; ++f) s[q][f][c + PP * k] = col[f][k];
+                                            });
         const T *D = a.D;
 #pragma unroll
         for (int f = 0; f < 8; ++f)
 #pragma unroll
             for (int k = 0; k < P; ++k) {
-                T d = 0;
-#pragma unroll
-                for (int m = 0; m < P; ++m) d += D[k * P + m] * col[f][m];
-                dz[f][k] = d;
+                dz[f][k] = dot<P>(D + k * P, [&](int m) { return col[f][m]; });
             }
     }
     __syncthreads();  // tiles complete
     T res[P][5];
     if (act) {
-        T Di[P], Dj[P];
-#pragma unroll
-        for (int m = 0; m < P; ++m) {
-            Di[m] = a.D[i * P + m];
-            Dj[m] = a.D[j * P + m];
-        }
 #pragma unroll
         for (int k = 0; k < P; ++k) {
             T mx[10];
@@ -494,37 +518,23 @@ __global__ __launch_bounds__((col_threads<N, T>()), (col_blocks<N, T, MODE>())) 
             T dd[8][3];
 #pragma unroll
             for (int f = 0; f < 8; ++f) {
-                T da = 0, db = 0;
-#pragma unroll
-                for (int m = 0; m < P; ++m) {
-                    da += Di[m] * s[q][f][m + P * (j + P * k)];
-                    db += Dj[m] * s[q][f][i + P * (m + P * k)];
-                }
-                dd[f][0] = da;
-                dd[f][1] = db;
+                dd[f][0] = dot<P>(Di, [&](int m) { return s[q][f][m + P * (j + P * k)]; });
+                dd[f][1] = dot<P>(Dj, [&](int m) { return s[q][f][i + P * (m + P * k)]; });
                 dd[f][2] = dz[f][k];
             }
             const int l = c + PP * k;
-            // node_combine with 1/rho and rho'/rho already formed
             const T uu = s[q][3][l], vv = s[q][4][l], ww = s[q][5][l];
-            T Uc[3];
-            Uc[0] = uu * mx[0];
-            Uc[1] = vv * mx[4];
-            Uc[2] = uu * mx[6] + vv * mx[7] + ww * mx[8];
-            auto cart = [&](int f, int cc) -> T {
-                if (cc == 0) return dd[f][0] * mx[0] + dd[f][2] * mx[6];
-                if (cc == 1) return dd[f][1] * mx[4] + dd[f][2] * mx[7];
-                return dd[f][2] * mx[8];
-            };
-            auto adv = [&](int f) -> T { return Uc[0] * dd[f][0] + Uc[1] * dd[f][1] + Uc[2] * dd[f][2]; };
-            const T gz = (T)(-a.g0);
             const T bk = F64 ? buoy[k] * irho[k] : buoy[k];
-            T R[5];
-            R[0] = -(cart(0, 0) + cart(1, 1) + cart(2, 2));
-            R[1] = -adv(3) - cart(7, 0) * irho[k];
-            R[2] = -adv(4) - cart(7, 1) * irho[k];
-            R[3] = -adv(5) - cart(7, 2) * irho[k] + bk * gz;
-            R[4] = -adv(6);
+            T R[5], dm[5][3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                dm[0][d] = dd[7][d];
+#pragma unroll
+                for (int f = 1; f < 5; ++f) dm[f][d] = dd[2 + f][d];
+            }
+            box_momentum<T>(mx, uu, vv, ww, dm, irho[k], bk, (T)(-a.g0), R + 1);
+            const T dzm[3] = {dd[0][2], dd[1][2], dd[2][2]};
+            R[0] = box_mass<T>(mx, dd[0][0], dd[1][1], dzm);
             // J w R, or J w (q_s + cdt R) away from the walls when folding
             const bool wall = it.walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
             if (F64 && B.fold && !wall) {
@@ -583,12 +593,13 @@ __global__ __launch_bounds__((col_threads<N, T>()), (col_blocks<N, T, MODE>())) 
 // waves per SIMD.
 template <int N, typename T> constexpr int col2_waves()
 {
-    return sizeof(T) == 4 ? 4 : (N <= 3 ? 4 : (N == 4 ? 3 : 2));
+    return sizeof(T) == 4 ? 4 : (N <= 2 ? 4 : (N <= 4 ? 3 : 2));
 }
 // doubles after each element's tile: at N = 4, 8 spread the xi and eta rows of
 // the two or three elements a wavefront spans over the LDS banks (50,640
 // bytes, still three workgroups per CU); at N = 3 the 40 KB tile has no room
 template <int N, typename T = double> constexpr int col2_pad() { return sizeof(T) == 8 && N == 4 ? 8 : 0; }
+template <int N, typename T> constexpr int col2_group() { return N + 1; }
 // N = 5, 6 (seven and five elements per 256-lane workgroup, 60 and 69 KB of
 // LDS): two waves per SIMD
 template <int N, typename T = double>
@@ -616,6 +627,12 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
     T ir[P], bq[P];
     double c0 = 0.0, c1 = 0.0, c2 = 0.0, c3 = 0.0;
     int ez = 0;
+    T Di[P], Dj[P];
+#pragma unroll
+    for (int m = 0; m < P; ++m) {
+        Di[m] = a.D[i * P + m];
+        Dj[m] = a.D[j * P + m];
+    }
     if (act) {
         const BoxElem be = box_elem((uint32_t)(e0 + q), a.fx, a.fy);
         ez = be.ez;
@@ -628,35 +645,24 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
         if (gi == a.ni) gi = 0;
         if (gj == a.nj) gj = 0;
         const int base = gi + a.ni * gj, layer = a.ni * a.nj;
+        gather_column<P, col2_group<N, T>()>(a, it.theta0, base, layer, be.ez * N,
+                                             [&](int k, const double *qv, double rb, double pp) {
+                                                 const int l = c + PP * k;
+                                                 rho[k] = rb + qv[0];
+                                                 S(q, 0, l) = (T)pp;
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-            int gk = be.ez * N + k;
-            if (gk == a.nk) gk = 0;
-            const int32_t I = base + layer * gk;
-            const double *qp = a.q + I, *rf = a.ref + I;
-            const double r_ = qp[0], u = qp[a.nu], v = qp[2 * a.nu], w = qp[3 * a.nu], tp = qp[4 * a.nu];
-            const double rb = rf[0], tb = it.theta0, pb = rf[2 * a.nu];
-            rho[k] = rb + r_;
-            const double dl = r_ * tb + rb * tp + r_ * tp;
-            const int l = c + PP * k;
-            S(q, 0, l) = (T)(pb * eos_rel(dl / (rb * tb), a.gamma, a.eos));
-            S(q, 1, l) = (T)u;
-            S(q, 2, l) = (T)v;
-            S(q, 3, l) = (T)w;
-            S(q, 4, l) = (T)tp;
-            const double ird = 1.0 / rho[k];
-            ir[k] = (T)ird;
-            bq[k] = F64 ? (T)r_ : (T)(r_ * ird);
-        }
+                                                 for (int v = 1; v < 5; ++v) S(q, v, l) = (T)qv[v];
+                                                 if constexpr (F64) {
+                                                     bq[k] = qv[0];
+                                                 } else {
+                                                     const double ird = 1.0 / rho[k];
+                                                     ir[k] = (T)ird;
+                                                     bq[k] = (T)(qv[0] * ird);
+                                                 }
+                                             });
     }
     __syncthreads();  // first tile complete
     T res[P][5];
-    T Di[P], Dj[P];
-#pragma unroll
-    for (int m = 0; m < P; ++m) {
-        Di[m] = a.D[i * P + m];
-        Dj[m] = a.D[j * P + m];
-    }
     if (act) {
 #pragma unroll
         for (int k = 0; k < P; ++k) {
@@ -667,28 +673,14 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
             T dd[5][3];
 #pragma unroll
             for (int f = 0; f < 5; ++f) {
-                T da = 0, db = 0, dz = 0;
-#pragma unroll
-                for (int m = 0; m < P; ++m) {
-                    da += Di[m] * S(q, f, m + P * (j + P * k));
-                    db += Dj[m] * S(q, f, i + P * (m + P * k));
-                    dz += a.D[k * P + m] * S(q, f, c + PP * m);
-                }
-                dd[f][0] = da;
-                dd[f][1] = db;
-                dd[f][2] = dz;
+                dd[f][0] = dot<P>(Di, [&](int m) { return S(q, f, m + P * (j + P * k)); });
+                dd[f][1] = dot<P>(Dj, [&](int m) { return S(q, f, i + P * (m + P * k)); });
+                dd[f][2] = dot<P>(a.D + k * P, [&](int m) { return S(q, f, c + PP * m); });
             }
-            T Uc[3];
-            Uc[0] = uu * mx[0];
-            Uc[1] = vv * mx[4];
-            Uc[2] = uu * mx[6] + vv * mx[7] + ww * mx[8];
-            auto adv = [&](int f) -> T { return Uc[0] * dd[f][0] + Uc[1] * dd[f][1] + Uc[2] * dd[f][2]; };
+            if constexpr (F64) ir[k] = (T)(1.0 / rho[k]);
             const T bk = F64 ? bq[k] * ir[k] : bq[k];
             T R[4];
-            R[0] = -adv(1) - (dd[0][0] * mx[0] + dd[0][2] * mx[6]) * ir[k];
-            R[1] = -adv(2) - (dd[0][1] * mx[4] + dd[0][2] * mx[7]) * ir[k];
-            R[2] = -adv(3) - dd[0][2] * mx[8] * ir[k] + bk * gz;
-            R[3] = -adv(4);
+            box_momentum<T>(mx, uu, vv, ww, dd, ir[k], bk, (T)gz, R);
             const bool wall = walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
             if (fold && !wall) {
                 const T qv[4] = {uu, vv, ww, tt};
@@ -726,15 +718,12 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
         for (int k = 0; k < P; ++k) {
             T mx[10];
             box_node_metric<T>(a.bm, ez, B.xi[k], c0 * B.w[k], c1, c2, c3, mx);
-            T da = 0, db = 0, dz[3] = {0, 0, 0};
+            const T da = dot<P>(Di, [&](int m) { return S(q, 0, m + P * (j + P * k)); });
+            const T db = dot<P>(Dj, [&](int m) { return S(q, 1, i + P * (m + P * k)); });
+            T dz[3];
 #pragma unroll
-            for (int m = 0; m < P; ++m) {
-                da += Di[m] * S(q, 0, m + P * (j + P * k));
-                db += Dj[m] * S(q, 1, i + P * (m + P * k));
-#pragma unroll
-                for (int f = 0; f < 3; ++f) dz[f] += a.D[k * P + m] * fl[m][f];
-            }
-            const T R0 = -((da * mx[0] + dz[0] * mx[6]) + (db * mx[4] + dz[1] * mx[7]) + dz[2] * mx[8]);
+            for (int f = 0; f < 3; ++f) dz[f] = dot<P>(a.D + k * P, [&](int m) { return fl[m][f]; });
+            const T R0 = box_mass<T>(mx, da, db, dz);
             const bool wall = walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
             res[k][0] = (fold && !wall) ? mx[9] * fma((T)cdt, R0, bq[k]) : mx[9] * R0;
         }
@@ -861,8 +850,9 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
         const int ex = gi / N;
         const bool xface = gi % N == 0;
         // the face rows' copies (absent ones are not loaded) are loaded
-        // together, then summed; the run-start x copies (Fb, at most one
-        // node in EB N of a row) after them
+        // together; the run-start x copies (Fb, at most one node in EB N of a
+        // row) only where there are any.  The sum: x pairs first, then over y
+        // and z, as the gather finish (box_finish_node) takes it
         T ca[2][2][5];
 #pragma unroll
         for (int z = 0; z < 2; ++z)
@@ -873,13 +863,6 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
 #pragma unroll
                 for (int v = 0; v < 5; ++v) ca[z][y][v] = has ? Fa[o * 5 + v] : (T)0;
             }
-#pragma unroll
-        for (int z = 0; z < 2; ++z)
-#pragma unroll
-            for (int y = 0; y < 2; ++y)
-                if (z < nzc && y < nyc)
-#pragma unroll
-                    for (int v = 0; v < 5; ++v) r[v] += (double)ca[z][y][v];
         if (xface) {
 #pragma unroll
             for (int z = 0; z < 2; ++z)
@@ -889,10 +872,17 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
                     if (z < nzc && y < nyc && (ex == 0 || ec % EB == 0)) {
                         const int64_t ob = ((int64_t)(ex == 0 ? ec + nx - 1 : ec - 1) * NB + split_fp<N>(jc[y], kc[z])) * 5;
 #pragma unroll
-                        for (int v = 0; v < 5; ++v) r[v] += (double)Fb[ob + v];
+                        for (int v = 0; v < 5; ++v) ca[z][y][v] += Fb[ob + v];
                     }
                 }
         }
+#pragma unroll
+        for (int z = 0; z < 2; ++z)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+                if (z < nzc && y < nyc)
+#pragma unroll
+                    for (int v = 0; v < 5; ++v) r[v] += (double)ca[z][y][v];
     } else {
         if constexpr (NIP == 0) {
             return;
@@ -923,7 +913,7 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
                 c1[v] = i == 0 ? Fb[o1 + v] : (T)0;
             }
 #pragma unroll
-            for (int v = 0; v < 5; ++v) r[v] = i == 0 ? (double)c0[v] + (double)c1[v] : (double)c0[v];
+            for (int v = 0; v < 5; ++v) r[v] = (double)(c0[v] + c1[v]);  // absent: zero
         }
     }
 #pragma unroll
@@ -1036,37 +1026,26 @@ __global__ __launch_bounds__((col_threads<N, T>())) void k_elem_stream(Batch B)
         if (gi == a.ni) gi = 0;
         if (gj == a.nj) gj = 0;
         const int base = gi + a.ni * gj, layer = a.ni * a.nj;
+        gather_column<P, stream_group<N, T>()>(
+            a, it.theta0, base, layer, be.ez * N, [&](int k, const double *qv, double rb, double pp) {
+                const double rho = rb + qv[0], ir = 1.0 / rho;
+                irho[k] = (T)ir;
+                buoy[k] = (T)(qv[0] * ir);
+                T mx[10];
+                box_node_metric<T>(a.bm, ez, B.xi[k], c0, c1, c2, c3, mx);
+                const T uu = (T)qv[1], vv = (T)qv[2], ww = (T)qv[3];
+                Uc[k][0] = uu * mx[0];
+                Uc[k][1] = vv * mx[4];
+                Uc[k][2] = fm(ww, mx[8], fm(vv, mx[7], uu * mx[6]));
+                const int l = c + PP * k;
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-            int gk = be.ez * N + k;
-            if (gk == a.nk) gk = 0;
-            const int32_t I = base + layer * gk;
-            const double *qp = a.q + I, *rf = a.ref + I;
-            const double rp = qp[0], u = qp[a.nu], v = qp[2 * a.nu], w = qp[3 * a.nu], tp = qp[4 * a.nu];
-            const double rb = rf[0], tb = it.theta0, pb = rf[2 * a.nu];
-            const double rho = rb + rp;
-            // p' = p_bar ((rho theta / rho_bar theta_bar)^gamma - 1) without cancellation
-            const double dl = rp * tb + rb * tp + rp * tp;
-            const double pp = pb * eos_rel(dl / (rb * tb), a.gamma, a.eos);
-            const double ir = 1.0 / rho;
-            irho[k] = (T)ir;
-            buoy[k] = (T)(rp * ir);
-            T mx[10];
-            box_node_metric<T>(a.bm, ez, B.xi[k], c0, c1, c2, c3, mx);
-            const T uu = (T)u, vv = (T)v, ww = (T)w;
-            Uc[k][0] = uu * mx[0];
-            Uc[k][1] = vv * mx[4];
-            Uc[k][2] = uu * mx[6] + vv * mx[7] + ww * mx[8];
-            const int l = c + PP * k;
-            s[q][0][l] = (T)(rho * u);
-            s[q][1][l] = (T)(rho * v);
-            s[q][2][l] = (T)(rho * w);
-            s[q][3][l] = uu;
-            s[q][4][l] = vv;
-            s[q][5][l] = ww;
-            s[q][6][l] = (T)tp;
-            s[q][7][l] = (T)pp;
-        }
+                for (int v = 0; v < 3; ++v) s[q][v][l] = (T)(rho * qv[1 + v]);
+                s[q][3][l] = uu;
+                s[q][4][l] = vv;
+                s[q][5][l] = ww;
+                s[q][6][l] = (T)qv[4];
+                s[q][7][l] = (T)pp;
+            });
     }
     __syncthreads();  // tiles complete
     T R[P][5];
@@ -1086,27 +1065,21 @@ __global__ __launch_bounds__((col_threads<N, T>())) void k_elem_stream(Batch B)
             for (int m = 0; m < P; ++m) cf[m] = s[q][f][c + PP * m];
 #pragma unroll
             for (int k = 0; k < P; ++k) {
-                const double omz = 1.0 - ((double)ez + 0.5 * (1.0 + B.xi[k])) * a.bm.inz;  // 1 - z/H
+                const double omz = fm(-fm(0.5, 1.0 + B.xi[k], (double)ez), a.bm.inz, 1.0);  // 1 - z/H
                 const T mx6 = (T)(omz * c2), mx7 = (T)(omz * c3);
-                T dc = 0, da = 0, db = 0;
-#pragma unroll
-                for (int m = 0; m < P; ++m) dc += D[k * P + m] * cf[m];
-                if (f != 1 && f != 2) {
-#pragma unroll
-                    for (int m = 0; m < P; ++m) da += Di[m] * s[q][f][m + P * (j + P * k)];
-                }
-                if (f != 0 && f != 2) {
-#pragma unroll
-                    for (int m = 0; m < P; ++m) db += Dj[m] * s[q][f][i + P * (m + P * k)];
-                }
-                if (f == 0) R[k][0] = da * mx0 + dc * mx6;                // d(rho u)/dx
-                if (f == 1) R[k][0] = R[k][0] + (db * mx4 + dc * mx7);    // + d(rho v)/dy
-                if (f == 2) R[k][0] = -(R[k][0] + dc * mx8);              // + d(rho w)/dz
-                if (f >= 3 && f <= 6) R[k][f - 2] = -(Uc[k][0] * da + Uc[k][1] * db + Uc[k][2] * dc);
+                T da = 0, db = 0;
+                const T dc = dot<P>(D + k * P, [&](int m) { return cf[m]; });
+                if (f != 1 && f != 2) da = dot<P>(Di, [&](int m) { return s[q][f][m + P * (j + P * k)]; });
+                if (f != 0 && f != 2) db = dot<P>(Dj, [&](int m) { return s[q][f][i + P * (m + P * k)]; });
+                // the operations of box_mass and box_momentum, a field at a time
+                if (f == 0) R[k][0] = fm(dc, mx6, da * mx0);              // d(rho u)/dx
+                if (f == 1) R[k][0] = R[k][0] + fm(dc, mx7, db * mx4);    // + d(rho v)/dy
+                if (f == 2) R[k][0] = -fm(dc, mx8, R[k][0]);              // + d(rho w)/dz
+                if (f >= 3 && f <= 6) R[k][f - 2] = -fm(Uc[k][2], dc, fm(Uc[k][1], db, Uc[k][0] * da));
                 if (f == 7) {
-                    R[k][1] = R[k][1] - (da * mx0 + dc * mx6) * irho[k];
-                    R[k][2] = R[k][2] - (db * mx4 + dc * mx7) * irho[k];
-                    R[k][3] = R[k][3] - (dc * mx8) * irho[k] + buoy[k] * (T)(-a.g0);
+                    R[k][1] = fm(-fm(dc, mx6, da * mx0), irho[k], R[k][1]);
+                    R[k][2] = fm(-fm(dc, mx7, db * mx4), irho[k], R[k][2]);
+                    R[k][3] = fm(buoy[k], (T)(-a.g0), fm(-(dc * mx8), irho[k], R[k][3]));
                 }
             }
         }
@@ -1299,7 +1272,7 @@ int64_t split_item(const Mesh &m, int eb, BatchItem &it)
 template <int N, typename T, int SEG>
 int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, int mode)
 {
-    const bool colour = mode == 1, split = mode == 2;
+    const bool colour = mode == kColour, split = mode == kSplit, node = mode == kNode;
     Batch B;
     B.n = n;
     B.ca = items[0].c.a;
@@ -1313,16 +1286,17 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
     eos_coeffs(B.gamma, B.eos);
     // the recomputed metric runs a column kernel, EB elements per workgroup:
     // registers for every field's column up to N = 4, the streaming variant
-    // above (FP64 at N = 7, 8 outgrows both: one node per lane there)
+    // above (FP64 at N = 7, 8 outgrows both: one node per lane there, as with
+    // the stored metric and in kNode launches)
     constexpr int kind = N <= 4 ? 0 : (sizeof(T) == 4 || N <= 6 ? 1 : 2);
     constexpr bool col_ok = kind != 2;
     const bool recompute = items[0].mesh->metric_mode == NUMA_METRIC_RECOMPUTE;
-    const bool col = recompute && col_ok;
+    const bool col = recompute && col_ok && !node;
     const int eb = split ? split_eb<N>() : col ? col_eb<N, T>() : 1;
     // FP64 update that uses q_s (b != 0): the column and one-node-per-lane
     // element kernels fold q_s into the contributions (the streaming one,
     // which runs at its register limit, does not)
-    B.fold = (std::is_same<T, double>::value && B.cb != 0.0 && (split || !(recompute && kind == 1))) ? 1 : 0;
+    B.fold = (std::is_same<T, double>::value && B.cb != 0.0 && (split || !(col && kind == 1))) ? 1 : 0;
     int64_t eo = 0, bo = 0;
     for (int k = 0; k < n; ++k) {
         const Mesh &m = *items[k].mesh;
@@ -1346,9 +1320,9 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
         it.walls = m.walls ? 1 : 0;
         it.fx = fast_div((uint32_t)m.d.ne[0]);
         it.fy = fast_div((uint32_t)m.d.ne[1]);
-        // the gather finish's segments (a split item's x extent need not hold
-        // one: its fields are set below)
-        const int nseg = m.d.ne[0] / SEG > 0 ? m.d.ne[0] / SEG : 1;
+        // the gather finish's segments, the last one of a row partly empty
+        // where SEG does not divide nx (a split item's fields are set below)
+        const int nseg = (m.d.ne[0] + SEG - 1) / SEG;
         it.fseg = fast_div((uint32_t)nseg);
         const int64_t mblk = (int64_t)nseg * m.d.ne[1] * m.d.ne[2];
         it.mblk = (int)mblk;
@@ -1369,7 +1343,7 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
             bo += split_item(m, eb, it);
         } else {
             eo += (m.ne + eb - 1) / eb * eb;
-            bo += mblk + (m.walls ? (int64_t)(m.d.ne[0] / SEG) * m.d.ne[1] : 0);
+            bo += mblk + (m.walls ? (int64_t)nseg * m.d.ne[1] : 0);
         }
     }
     if (eo >= (int64_t(1) << 31) || bo >= (int64_t(1) << 31)) {
@@ -1415,6 +1389,8 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
         if (!recompute) {
             hipLaunchKernelGGL((k_elem_batch<N, T, kMetricStored>), dim3((unsigned)eo), dim3(block_threads<N>()), 0, s,
                                B);
+        } else if (node) {
+            hipLaunchKernelGGL((k_elem_batch<N, T, kMetricBox>), dim3((unsigned)eo), dim3(block_threads<N>()), 0, s, B);
         } else if constexpr (kind == 0) {
             hipLaunchKernelGGL((k_elem_col<N, T>), dim3((unsigned)(eo / eb)), dim3(col_threads<N, T>()), 0, s, B, 0);
         } else if constexpr (kind == 1) {
@@ -1430,32 +1406,38 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
     return NUMA_OK;
 }
 
-// The finish segment of a launch: the widest (seg_wide) that divides the x
-// element count of every item, halving down to seg_for, which divides every
-// batchable mesh's.  At N = 3 a 4-element segment is 12 lattice points, 96 of
-// every 128 bytes of a state line; 16 elements are 48 points, three whole
-// lines (measured at 64x64x16: finish 82 -> 61 us).  The per-node code and
-// its order of the copies do not depend on the segment: results are the
-// same bit for bit whichever segment a launch takes.
-template <int N> constexpr int seg_wide() { return N == 3 ? 16 : seg_for<N>(); }
+// The finish segment of a launch: the widest of three whose last segment
+// leaves at most a quarter of a row's lanes idle on every item, else the
+// narrowest.  At N = 3 a 4-element segment is 12 lattice points, 96 of every
+// 128 bytes of a state line; 16 elements are 48 points, three whole lines
+// (measured at 64x64x16: finish 82 -> 61 us); at N = 1, 2 the narrow segment
+// fills 4 and 32 lanes of a wavefront.  The per-node code and its order of the
+// copies do not depend on the segment: results are the same bit for bit
+// whichever segment a launch takes.
+template <int N> constexpr int seg_wide() { return N == 1 ? 64 : N <= 3 ? 16 : seg_for<N>(); }
+template <int N> constexpr int seg_mid() { return N == 1 ? 16 : N <= 3 ? 8 : seg_for<N>(); }
 
 template <int N>
 int pick_seg(const StepItem *items, int n)
 {
-    int seg = seg_wide<N>();
-    for (int k = 0; k < n; ++k)
-        while (seg > seg_for<N>() && items[k].mesh->d.ne[0] % seg) seg /= 2;
-    return seg;
+    for (const int seg : {seg_wide<N>(), seg_mid<N>()}) {
+        bool ok = true;
+        for (int k = 0; k < n; ++k) {
+            const int nx = items[k].mesh->d.ne[0];
+            ok = ok && 4 * ((nx + seg - 1) / seg * seg) <= 5 * nx;
+        }
+        if (ok) return seg;
+    }
+    return seg_for<N>();
 }
 
 template <int N, typename T>
 int32_t run_chunk(const StepItem *items, int n, int phase, hipStream_t s, int mode)
 {
     if constexpr (seg_wide<N>() != seg_for<N>()) {
-        static_assert(seg_wide<N>() == 4 * seg_for<N>(), "segments 4x, 2x and 1x of the narrowest");
         const int seg = pick_seg<N>(items, n);
         if (seg == seg_wide<N>()) return run_chunk_seg<N, T, seg_wide<N>()>(items, n, phase, s, mode);
-        if (seg == 2 * seg_for<N>()) return run_chunk_seg<N, T, 2 * seg_for<N>()>(items, n, phase, s, mode);
+        if (seg == seg_mid<N>()) return run_chunk_seg<N, T, seg_mid<N>()>(items, n, phase, s, mode);
     }
     return run_chunk_seg<N, T, seg_for<N>()>(items, n, phase, s, mode);
 }
@@ -1483,11 +1465,12 @@ int32_t run_plain_finish_seg(const Mesh &m, const double *ev, double *q, hipStre
     it.walls = m.walls ? 1 : 0;
     it.fx = fast_div((uint32_t)m.d.ne[0]);
     it.fy = fast_div((uint32_t)m.d.ne[1]);
-    it.fseg = fast_div((uint32_t)(m.d.ne[0] / SEG));
-    const int64_t mblk = (int64_t)(m.d.ne[0] / SEG) * m.d.ne[1] * m.d.ne[2];
+    const int nseg = (m.d.ne[0] + SEG - 1) / SEG;
+    it.fseg = fast_div((uint32_t)nseg);
+    const int64_t mblk = (int64_t)nseg * m.d.ne[1] * m.d.ne[2];
     it.mblk = (int)mblk;
     it.ne = (int)m.ne;
-    const int64_t bo = mblk + (m.walls ? (int64_t)(m.d.ne[0] / SEG) * m.d.ne[1] : 0);
+    const int64_t bo = mblk + (m.walls ? (int64_t)nseg * m.d.ne[1] : 0);
     const int threads = ((SEG * N * N * N + 63) / 64) * 64;
     hipLaunchKernelGGL((k_fin_batch<N, SEG, double, true>), dim3((unsigned)bo), dim3(threads), 0, s, B);
     NUMA_HIP(hipGetLastError());
@@ -1502,7 +1485,7 @@ int32_t run_plain_finish(const Mesh &m, const double *ev, double *q, hipStream_t
     if constexpr (seg_wide<N>() != seg_for<N>()) {
         const int seg = pick_seg<N>(&it, 1);
         if (seg == seg_wide<N>()) return run_plain_finish_seg<N, seg_wide<N>()>(m, ev, q, s);
-        if (seg == 2 * seg_for<N>()) return run_plain_finish_seg<N, 2 * seg_for<N>()>(m, ev, q, s);
+        if (seg == seg_mid<N>()) return run_plain_finish_seg<N, seg_mid<N>()>(m, ev, q, s);
     }
     return run_plain_finish_seg<N, seg_for<N>()>(m, ev, q, s);
 }
@@ -1648,32 +1631,64 @@ bool split_ok(const Mesh &m, int32_t prec)
     return mode && m.d.kind == NUMA_MESH_BOX && m.metric_mode == NUMA_METRIC_RECOMPUTE && m.N <= nmax;
 }
 
+// NUMA_STAGE_AUTO: how a launch of nl element-local nodes in all runs a stage.
+// A workgroup of the column kernels is a long chain of dependent LDS reads and
+// multiply-adds per lane (N = 4: 13 us for one workgroup alone, 4.5 us with one
+// node per lane), which a large launch hides behind other workgroups and a
+// small one does not; the split DSS moves fewest bytes and has the longer chain
+// of the two column kernels.  Measured at the lines, us per step, recomputed
+// metric (N: nodes, the routes' times):
+//   FP64 node / gather / split: 1: 25 k 30 / 30 / 45, 524 k 148 / 73 / 74, 1.05 M
+//   272 / 118 / 116; 2: 83 k 34 / 35 / 50, 1.8 M 228 / 156 / 162, 3.5 M 450 /
+//   318 / 284; 3: 197 k 44 / 43 / 51, 524 k 76 / 69 / 73, 786 k 100 / 94 / 90;
+//   FP64 node / split: 4: 512 k 82 / 86, 1.02 M 127 / 130, 1.28 M 154 / 141; 5: 885 k
+//   124 / 145, 1.8 M 217 / 225, 2.7 M 346 / 315; 6: 527 k 118 / 125, 615 k 135 / 128;
+//   7: 655 k 120 / 134, 786 k 135 / 139, 1.05 M 153 / 149; 8: 560 k 131 / 153, 746 k
+//   169 / 162; at 64 elements, N = 1..8: 25-51 / 28-58 / 43-100.
+//   Mixed node / gather: 3: 131 k 34 / 37, 197 k 38 / 38; 4: 256 k 48 / 48, 384 k 58 /
+//   60, 512 k 66 / 64; 5: 442 k 66 / 69, 885 k 104 / 107, 1.3 M 141 / 135; 6: 351 k
+//   65 / 71, 527 k 85 / 84; 7: 1.05 M 122 / 134, 2.1 M 223 / 228, 2.6 M 314 / 302;
+//   8: 746 k 113 / 122, 1.5 M 189 / 202, 3.0 M 416 / 377.
+int auto_route(int N, int32_t prec, int64_t nl)
+{
+    //                                     N = 1      2       3        4        5       6        7        8
+    static const int64_t node64[9] = {0, 28000, 95000, 200000, 1050000, 2000000, 570000, 850000, 620000};
+    static const int64_t gather64[4] = {0, 800000, 2300000, 620000};
+    static const int64_t nodemx[9] = {0, 28000, 90000, 190000, 400000, 1000000, 450000, 2300000, 1800000};
+    if (prec == NUMA_PREC_MIXED) return nl < nodemx[N] ? kNode : kGather;
+    if (nl < node64[N]) return kNode;
+    return N <= 3 && nl < gather64[N] ? kGather : kSplit;
+}
+
 int32_t launch_batch_stage(const StepItem *items, int n, int32_t prec, int phase, hipStream_t s)
 {
     // items the fused block kernels take (pencil.hip), the colour passes, the
-    // split DSS, the rest; partitioned in chunks on the stack, with no host
-    // allocation
+    // split DSS, the rest, the small ones; partitioned in chunks on the stack,
+    // with no host allocation.  The items of NUMA_STAGE_AUTO choose together,
+    // by what they add up to: either way gives an item the same result.
     constexpr int kChunk = 4 * kMaxBatch;
-    StepItem part[4][kChunk];
+    StepItem part[5][kChunk];
+    int64_t nl = 0;
+    for (int k = 0; k < n; ++k)
+        if (items[k].mesh->stage_mode == NUMA_STAGE_AUTO) nl += items[k].mesh->nl;
     for (int c0 = 0; c0 < n; c0 += kChunk) {
         const int cn = n - c0 < kChunk ? n - c0 : kChunk;
-        int cnt[4] = {0, 0, 0, 0};
+        int cnt[5] = {0, 0, 0, 0, 0};
         for (int k = c0; k < c0 + cn; ++k) {
             const Mesh &m = *items[k].mesh;
-            const int g = pencil_stage_ok(items[k], prec) ? 0 : colour_ok(m) ? 1 : split_ok(m, prec) ? 2 : 3;
-            if (g == 3 && !box_batchable(m)) {
-                set_error("batched stage: a box mesh whose x element count does not fit the finish segment");
-                return NUMA_EUNSUPPORTED;
-            }
+            const int g = pencil_stage_ok(items[k], prec)       ? 4
+                          : colour_ok(m)                        ? kColour
+                          : m.stage_mode != NUMA_STAGE_AUTO     ? (split_ok(m, prec) ? kSplit : kGather)
+                          : m.metric_mode == NUMA_METRIC_STORED ? kNode
+                                                                : auto_route(m.N, prec, nl);
             part[g][cnt[g]++] = items[k];
         }
         int32_t rc;
-        if (cnt[0] && (rc = launch_pencil_stage(part[0], cnt[0], prec, phase, s))) return rc;
-        for (int g = 1; g < 4; ++g) {
+        if (cnt[4] && (rc = launch_pencil_stage(part[4], cnt[4], prec, phase, s))) return rc;
+        for (const int g : {kColour, kSplit, kGather, kNode}) {
             if (!cnt[g]) continue;
-            const int mode = g == 1 ? 1 : g == 2 ? 2 : 0;
-            rc = prec == NUMA_PREC_MIXED ? run_stage_t<float>(part[g], cnt[g], phase, s, mode)
-                                         : run_stage_t<double>(part[g], cnt[g], phase, s, mode);
+            rc = prec == NUMA_PREC_MIXED ? run_stage_t<float>(part[g], cnt[g], phase, s, g)
+                                         : run_stage_t<double>(part[g], cnt[g], phase, s, g);
             if (rc) return rc;
         }
     }

@@ -44,36 +44,6 @@ __global__ void k_rk_stage(int64_t n, StageCoef c, const double *qn, const doubl
     qout[a] = rk_update(c, c.a == 0.0 ? 0.0 : qn[a], qs[a], r[a]);
 }
 
-// Second half of a fused stage: DSS (mass-weighted), no-flux projection and
-// the stage update of every unique node.  Lanes walk the nodes in
-// first-occurrence order of the element scan (own[]), so a block gathers the
-// contributions of a few adjacent elements that its XCD has just read, and
-// its state reads and writes merge into whole cache lines across consecutive
-// blocks.  Copies are summed in ascending element-local order.  qout may alias
-// qs or qn (one lane per node).
-template <typename T>
-__global__ void k_stage_finish(PointArgs p, const int32_t *own, const int32_t *toff, const int32_t *tidx,
-                               const T *ev, StageCoef c, const double *qn, const double *qs, double *qout)
-{
-    int64_t t = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (t >= p.nu) return;
-    const int64_t I = own[t];
-    const int32_t b = toff[t], en = toff[t + 1];
-    double r[5] = {0, 0, 0, 0, 0};
-    for (int32_t c = b; c < en; ++c) {
-        const int64_t cc = tidx[c];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) r[v] += (double)ev[v * p.nl + cc];
-    }
-    const double mi = p.Minv[I];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) r[v] *= mi;
-    noflux(p, I, r[1], r[2], r[3]);
-#pragma unroll
-    for (int v = 0; v < 5; ++v)
-        qout[v * p.nu + I] = rk_update(c, c.a == 0.0 ? 0.0 : qn[v * p.nu + I], qs[v * p.nu + I], r[v]);
-}
-
 // Finish of a fused stage on the shell: one lane per unique node in unique
 // order I = h + n_h gk, so state reads and writes run along the horizontal
 // numbering.  The copies of a node factor: its horizontal copies in the
@@ -194,11 +164,9 @@ void launch_shell_finish_t(Mesh &m, const T *ev, const StageCoef &c, const doubl
 
 }  // namespace
 
-int32_t launch_dss(Mesh &m, int32_t nvar, const double *cin, double *out, int32_t flags, hipStream_t s,
-                   const double *minv)
+int32_t launch_dss(Mesh &m, int32_t nvar, const double *cin, double *out, int32_t flags, hipStream_t s)
 {
     PointArgs p = point_args(m);
-    if (minv) p.Minv = minv;
     hipLaunchKernelGGL(k_dss, dim3(nblocks(m.nu, 256)), dim3(256), 0, s, p, nvar, cin, out, flags);
     NUMA_HIP(hipGetLastError());
     return NUMA_OK;
@@ -231,22 +199,10 @@ int32_t launch_shell_plain_finish(Mesh &m, const double *ev, double *q, hipStrea
 int32_t launch_stage_finish(Mesh &m, int32_t prec, const StageCoef &c, const double *qn, const double *qs,
                             double *qout, hipStream_t s)
 {
-    if (m.d.kind == NUMA_MESH_SHELL) {  // node-major contributions (launch_stage_elements)
-        if (prec == NUMA_PREC_MIXED)
-            launch_shell_finish_t<float>(m, m.dv.ev32, c, qn, qs, qout, s);
-        else
-            launch_shell_finish_t<double>(m, m.dv.ev64, c, qn, qs, qout, s, shell_folds(m, prec, c) ? 1 : 0);
-        NUMA_HIP(hipGetLastError());
-        return NUMA_OK;
-    }
-    PointArgs p = point_args(m);
-    p.Minv = stage_minv(m);
     if (prec == NUMA_PREC_MIXED)
-        hipLaunchKernelGGL(k_stage_finish<float>, dim3(nblocks(m.nu, 256)), dim3(256), 0, s, p, m.dv.own, m.dv.toff,
-                           m.dv.tidx, m.dv.ev32, c, qn, qs, qout);
+        launch_shell_finish_t<float>(m, m.dv.ev32, c, qn, qs, qout, s);
     else
-        hipLaunchKernelGGL(k_stage_finish<double>, dim3(nblocks(m.nu, 256)), dim3(256), 0, s, p, m.dv.own, m.dv.toff,
-                           m.dv.tidx, m.dv.ev64, c, qn, qs, qout);
+        launch_shell_finish_t<double>(m, m.dv.ev64, c, qn, qs, qout, s, shell_folds(m, prec, c) ? 1 : 0);
     NUMA_HIP(hipGetLastError());
     return NUMA_OK;
 }

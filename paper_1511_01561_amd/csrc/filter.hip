@@ -34,8 +34,8 @@ struct FilterArgs {
     const double *met;    // [n_elem][10][np], J w in component 9
     const double *hcol;   // box: [nx*ny][4][(N+1)^2] column factors, J w_i w_j in factor 0
     const double *q;      // [5][n_unique]
-    double *c;            // J w (F q) at every element-local node
-    int64_t ne, nl, nu;
+    double *c;            // J w (F q) at every element-local node, node-major
+    int64_t ne, nu;
     int ni, nj, nk;       // box lattice extents (nk = -1 unless z is periodic)
     FastDiv fx, fy;       // division by the box element counts along x and y
     double w[kMaxP];      // GLL weights
@@ -62,12 +62,11 @@ constexpr int filter_threads()
 }
 
 // One lane per element-local node; the three directional passes alternate
-// between two LDS buffers of the block's elements.  NM: the contributions are
+// between two LDS buffers of the block's elements.  The contributions are
 // written node-major ([n_local][5], a copy's five values together, for the box
 // and shell finish kernels), staged in LDS so that the block's consecutive
-// elements go out as one run of 16-byte stores; else element-major
-// ([5][n_local], for the generic DSS).
-template <int N, bool NM, int GEO>
+// elements go out as one run of 16-byte stores.
+template <int N, int GEO>
 __global__ void __launch_bounds__(filter_threads<N>()) k_filter(FilterArgs a)
 {
     constexpr int P = N + 1, PP = P * P, NP = PP * P, EB = filter_eb<N>(), NE = EB * NP;
@@ -138,39 +137,29 @@ __global__ void __launch_bounds__(filter_threads<N>()) k_filter(FilterArgs a)
             r[v] = Jw * x;
         }
     }
-    if constexpr (!NM) {
-        if (on)
+    // s1 was last read before the previous barrier: reuse it as staging
+    double *st = &s1[0][0];
+    if (t < NE)
 #pragma unroll
-            for (int v = 0; v < 5; ++v) a.c[v * a.nl + e * NP + l] = r[v];
-    } else {
-        // s1 was last read before the previous barrier: reuse it as staging
-        double *st = &s1[0][0];
-        if (t < NE)
-#pragma unroll
-            for (int v = 0; v < 5; ++v) st[t * 5 + v] = r[v];
-        __syncthreads();
-        const int nel = a.ne - e0 < EB ? (int)(a.ne - e0) : EB;
-        store_run<double>(a.c + e0 * (NP * 5), st, nel * NP * 5, t, NT);
-    }
+        for (int v = 0; v < 5; ++v) st[t * 5 + v] = r[v];
+    __syncthreads();
+    const int nel = a.ne - e0 < EB ? (int)(a.ne - e0) : EB;
+    store_run<double>(a.c + e0 * (NP * 5), st, nel * NP * 5, t, NT);
 }
 
 template <int N, int GEO>
-void launch_filter_g(const FilterArgs &a, bool node_major, hipStream_t s)
+void launch_filter_g(const FilterArgs &a, hipStream_t s)
 {
     constexpr int EB = filter_eb<N>();
-    const unsigned blocks = (unsigned)((a.ne + EB - 1) / EB);
-    if (node_major)
-        hipLaunchKernelGGL((k_filter<N, true, GEO>), dim3(blocks), dim3(filter_threads<N>()), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_filter<N, false, GEO>), dim3(blocks), dim3(filter_threads<N>()), 0, s, a);
+    hipLaunchKernelGGL((k_filter<N, GEO>), dim3((unsigned)((a.ne + EB - 1) / EB)), dim3(filter_threads<N>()), 0, s, a);
 }
 
 template <int N>
-void launch_filter_n(const FilterArgs &a, int geo, bool node_major, hipStream_t s)
+void launch_filter_n(const FilterArgs &a, int geo, hipStream_t s)
 {
-    if (geo == kGeoStored) launch_filter_g<N, kGeoStored>(a, node_major, s);
-    else if (geo == kGeoBox) launch_filter_g<N, kGeoBox>(a, node_major, s);
-    else launch_filter_g<N, kGeoBoxCol>(a, node_major, s);
+    if (geo == kGeoStored) launch_filter_g<N, kGeoStored>(a, s);
+    else if (geo == kGeoBox) launch_filter_g<N, kGeoBox>(a, s);
+    else launch_filter_g<N, kGeoBoxCol>(a, s);
 }
 
 // Legendre P_0..P_N at x by the three-term recurrence.
@@ -224,7 +213,6 @@ int32_t launch_filter(Mesh &m, double order, int32_t cutoff, double *q, hipStrea
     a.q = q;
     a.c = m.dv.ev64;
     a.ne = m.ne;
-    a.nl = m.nl;
     a.nu = m.nu;
     const bool shell = m.d.kind == NUMA_MESH_SHELL;
     if (!shell) {
@@ -236,26 +224,26 @@ int32_t launch_filter(Mesh &m, double order, int32_t cutoff, double *q, hipStrea
     }
     for (int k = 0; k < m.P; ++k) a.w[k] = m.w[k];
     filter_matrix(m.N, m.xi, m.w, order, cutoff, a.F);
-    if (!shell && filter_split_ok(m)) return launch_filter_split(m, a.F, q, s);
+    // few nodes: one per lane and the gather finish, whose chains are shorter
+    // (as in a stage; both give the same result).  Pair at N = 4: 8 k nodes 10.5
+    // against 15.7 us, 128 k 12.1 / 16.0, 512 k 23.0 / 22.3, 1.02 M 36.3 / 34.2;
+    // N = 8: 47 k 14.1 / 24.1, 373 k 27.8 / 30.0, 746 k 40.9 / 40.0
+    const bool small = m.stage_mode == NUMA_STAGE_AUTO && m.nl < 450000;
+    if (!shell && filter_split_ok(m) && !small) return launch_filter_split(m, a.F, q, s);
     const int geo = shell ? kGeoStored : (m.metric_mode == NUMA_METRIC_RECOMPUTE ? kGeoBoxCol : kGeoBox);
-    // the box (x extent a multiple of the finish segment) and the shell sum
-    // node-major contributions with their stage finish kernels; other boxes
-    // take the generic DSS
-    const bool nm = shell || box_batchable(m);
+    // the box and the shell sum the contributions with their stage finish kernels
     switch (m.N) {
-    case 1: launch_filter_n<1>(a, geo, nm, s); break;
-    case 2: launch_filter_n<2>(a, geo, nm, s); break;
-    case 3: launch_filter_n<3>(a, geo, nm, s); break;
-    case 4: launch_filter_n<4>(a, geo, nm, s); break;
-    case 5: launch_filter_n<5>(a, geo, nm, s); break;
-    case 6: launch_filter_n<6>(a, geo, nm, s); break;
-    case 7: launch_filter_n<7>(a, geo, nm, s); break;
-    default: launch_filter_n<8>(a, geo, nm, s); break;
+    case 1: launch_filter_n<1>(a, geo, s); break;
+    case 2: launch_filter_n<2>(a, geo, s); break;
+    case 3: launch_filter_n<3>(a, geo, s); break;
+    case 4: launch_filter_n<4>(a, geo, s); break;
+    case 5: launch_filter_n<5>(a, geo, s); break;
+    case 6: launch_filter_n<6>(a, geo, s); break;
+    case 7: launch_filter_n<7>(a, geo, s); break;
+    default: launch_filter_n<8>(a, geo, s); break;
     }
     NUMA_HIP(hipGetLastError());
-    if (shell) return launch_shell_plain_finish(m, m.dv.ev64, q, s);
-    if (nm) return launch_box_plain_finish(m, m.dv.ev64, q, s);
-    return launch_dss(m, 5, m.dv.ev64, q, NUMA_DSS_MASS | NUMA_DSS_NOFLUX, s, stage_minv(m));
+    return shell ? launch_shell_plain_finish(m, m.dv.ev64, q, s) : launch_box_plain_finish(m, m.dv.ev64, q, s);
 }
 
 }  // namespace numa

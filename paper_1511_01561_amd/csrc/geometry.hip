@@ -531,11 +531,6 @@ int32_t launch_geometry(Mesh &m, hipStream_t s)
             NUMA_HIP(hipMemcpyAsync(v.hoff, m.hoff.data(), 4 * m.hoff.size(), hipMemcpyHostToDevice, s));
             NUMA_HIP(hipMemcpyAsync(v.hidx, m.hidx.data(), 4 * m.hidx.size(), hipMemcpyHostToDevice, s));
         }
-        if (v.own) {
-            NUMA_HIP(hipMemcpyAsync(v.own, m.own.data(), 4 * m.nu, hipMemcpyHostToDevice, s));
-            NUMA_HIP(hipMemcpyAsync(v.toff, m.toff.data(), 4 * (m.nu + 1), hipMemcpyHostToDevice, s));
-            NUMA_HIP(hipMemcpyAsync(v.tidx, m.tidx.data(), 4 * m.nl, hipMemcpyHostToDevice, s));
-        }
         m.D32.assign(m.D, m.D + m.P * m.P);
         NUMA_HIP(hipMemcpyAsync(v.D64, m.D, 8 * m.P * m.P, hipMemcpyHostToDevice, s));
         NUMA_HIP(hipMemcpyAsync(v.D32, m.D32.data(), 4 * m.P * m.P, hipMemcpyHostToDevice, s));

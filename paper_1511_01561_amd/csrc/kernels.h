@@ -30,15 +30,89 @@ constexpr int kEosTerms = 10;
 // log1p and expm1 would be hoisted out of the kernels' loops and held in
 // registers for the whole kernel.
 __device__ __noinline__ double eos_rel_large(double x, double gamma) { return expm1(gamma * log1p(x)); }
+__device__ __forceinline__ bool eos_small(double x) { return fabs(x) < 0.015625; }
+__device__ __forceinline__ double eos_series(double x, const double *c)
+{
+    double r = c[kEosTerms - 1];
+#pragma unroll
+    for (int k = kEosTerms - 2; k >= 0; --k) r = __builtin_fma(r, x, c[k]);
+    return r * x;
+}
 __device__ __forceinline__ double eos_rel(double x, double gamma, const double *c)
 {
-    if (fabs(x) < 0.015625) {
-        double r = c[kEosTerms - 1];
+    return eos_small(x) ? eos_series(x, c) : eos_rel_large(x, gamma);
+}
+
+// The per-node arithmetic of the box kernels, with every multiply-add written
+// out and contraction by the compiler off: the one-node-per-lane and the
+// column kernels evaluate a node with the same operations in the same order, so
+// their contributions are the same bit for bit, and a launch may take
+// whichever of them suits its size (a solve's result does not depend on what
+// it is batched with).
+__device__ __forceinline__ double fm(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fm(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// sum_m D_m f(m), m ascending
+template <int P, typename T, typename F>
+__device__ __forceinline__ T dot(const T *D, F f)
+{
+    T d = D[0] * f(0);
 #pragma unroll
-        for (int k = kEosTerms - 2; k >= 0; --k) r = r * x + c[k];
-        return r * x;
+    for (int m = 1; m < P; ++m) d = fm(D[m], f(m), d);
+    return d;
+}
+
+// rho theta / (rho_bar theta_bar) - 1 without cancellation; the pressure
+// perturbation is p' = p_bar ((rho theta / rho_bar theta_bar)^gamma - 1)
+__device__ __forceinline__ double box_eos_x(double rp, double tp, double rb, double tb)
+{
+#pragma clang fp contract(off)
+    return fm(rp, tp, fm(rb, tp, rp * tb)) / (rb * tb);
+}
+
+// p' of n nodes from x and p_bar: the series of every node first, in one piece
+// of straight-line code behind all of the nodes' loads (a branch per node
+// makes each node's loads wait for those of the node before), then the nodes
+// beyond it
+template <int M>
+__device__ __forceinline__ void eos_nodes(int n, const double *x, const double *pb, double gamma, const double *eos,
+                                          double *pp)
+{
+    bool small = true;
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+        if (k >= n) continue;
+        pp[k] = pb[k] * eos_series(x[k], eos);
+        small = small && eos_small(x[k]);
     }
-    return eos_rel_large(x, gamma);
+    if (!small)
+#pragma unroll
+        for (int k = 0; k < M; ++k)
+            if (k < n && !eos_small(x[k])) pp[k] = pb[k] * eos_rel_large(x[k], gamma);
+}
+
+// the momentum and theta' rows of R (R_u, R_v, R_w, R_theta') from the
+// reference derivatives dd of p', u, v, w, theta': advection in contravariant
+// form (u . grad f = sum_d U_d df/dxi_d), pressure gradient, buoyancy.  mx:
+// xi_x (0), eta_y (4), zeta_x, zeta_y, zeta_z (6..8); bk = rho'/rho
+template <typename T>
+__device__ __forceinline__ void box_momentum(const T *mx, T uu, T vv, T ww, const T (*dd)[3], T ir, T bk, T gz, T *R)
+{
+#pragma clang fp contract(off)
+    const T U0 = uu * mx[0], U1 = vv * mx[4], U2 = fm(ww, mx[8], fm(vv, mx[7], uu * mx[6]));
+    auto adv = [&](int f) -> T { return fm(U2, dd[f][2], fm(U1, dd[f][1], U0 * dd[f][0])); };
+    R[0] = -fm(fm(dd[0][2], mx[6], dd[0][0] * mx[0]), ir, adv(1));
+    R[1] = -fm(fm(dd[0][2], mx[7], dd[0][1] * mx[4]), ir, adv(2));
+    R[2] = fm(bk, gz, -fm(dd[0][2] * mx[8], ir, adv(3)));
+    R[3] = -adv(4);
+}
+
+// the mass row: da = d(rho u)/dxi, db = d(rho v)/deta, dz = d(rho u, rho v, rho w)/dzeta
+template <typename T>
+__device__ __forceinline__ T box_mass(const T *mx, T da, T db, const T *dz)
+{
+#pragma clang fp contract(off)
+    return -fm(dz[2], mx[8], fm(dz[0], mx[6], da * mx[0]) + fm(dz[1], mx[7], db * mx[4]));
 }
 
 // host: constants of the recomputed metric of a box mesh
@@ -184,8 +258,15 @@ __device__ __forceinline__ void node_gather(const RhsArgs<T> &a, int64_t e, int 
     }
     if constexpr (GEO == kMetricStored) {
         const T *mp = a.met + e * 10 * NP + l;
+        if constexpr (!SHELL) {
+            // the entries of the box metric that vary; xi_x and eta_y are
+            // constants of the mesh, the others zero for every terrain-following
+            // map (32 of 80 bytes per node)
+            in.mx[0] = (T)a.bm.ixa;
+            in.mx[4] = (T)a.bm.iyb;
+        }
 #pragma unroll
-        for (int c = 0; c < 10; ++c) in.mx[c] = mp[c * NP];
+        for (int c = SHELL ? 0 : 6; c < 10; ++c) in.mx[c] = mp[c * NP];
     }
     const double *qp = a.q + in.I;
     in.rp = qp[0];
@@ -205,10 +286,9 @@ __device__ __forceinline__ void node_stage(const RhsArgs<T> &a, int64_t e, int l
 {
     constexpr int NP = (N + 1) * (N + 1) * (N + 1);
     if (l >= NP) return;
-    const double rho = in.rb + in.rp;
-    // p' = p_bar ((rho theta / rho_bar theta_bar)^gamma - 1) without cancellation
-    const double dl = in.rp * in.tb + in.rb * in.tp + in.rp * in.tp;
-    const double pp = in.pb * eos_rel(dl / (in.rb * in.tb), a.gamma, a.eos);
+    const double rho = in.rb + in.rp, x = box_eos_x(in.rp, in.tp, in.rb, in.tb);
+    double pp;
+    eos_nodes<1>(1, &x, &in.pb, a.gamma, a.eos, &pp);
     s[0][l] = (T)(rho * in.u);
     s[1][l] = (T)(rho * in.v);
     s[2][l] = (T)(rho * in.w);
@@ -244,7 +324,8 @@ template <typename T>
 __device__ __forceinline__ void box_node_metric(const BoxMetric &bm, int ez, double zk, double c0, double c1, double c2,
                                                 double c3, T *mx)
 {
-    const double omz = 1.0 - ((double)ez + 0.5 * (1.0 + zk)) * bm.inz;  // 1 - z/H
+#pragma clang fp contract(off)
+    const double omz = fm(-fm(0.5, 1.0 + zk, (double)ez), bm.inz, 1.0);  // 1 - z/H
     mx[0] = (T)bm.ixa;
     mx[4] = (T)bm.iyb;
     mx[6] = (T)(omz * c2);
@@ -253,56 +334,33 @@ __device__ __forceinline__ void box_node_metric(const BoxMetric &bm, int ez, dou
     mx[9] = (T)c0;
 }
 
-// R at one node from the reference derivatives dd[f][d] of the tile fields
-// (d = xi, eta, zeta) and the metric mx: the chain rule, for the advected
-// fields directly in contravariant form, u . grad f = sum_d U_d df/dxi_d with
-// U_d = u . grad(xi_d).  With GEO == kMetricBox only the entries of the
-// box metric are read (xi_x, eta_y, zeta_x, zeta_y, zeta_z), and the
-// contractions the chain rule does not use are never formed.
-template <typename T, bool SHELL, int GEO>
-__device__ __forceinline__ void node_combine(const RhsArgs<T> &a, const T (*dd)[3], const T *mx, double u, double v,
-                                             double w, double rp, double rb, const T *gv, NodeOut<T> &o)
+// R at one shell node from the reference derivatives dd[f][d] of the tile
+// fields (d = xi, eta, zeta) and the metric mx: the chain rule, for the
+// advected fields directly in contravariant form, u . grad f = sum_d U_d
+// df/dxi_d with U_d = u . grad(xi_d).
+template <typename T>
+__device__ __forceinline__ void shell_combine(const T (*dd)[3], const T *mx, double u, double v, double w, double rp,
+                                              double rb, const T *gv, NodeOut<T> &o)
 {
     const T uu = (T)u, vv = (T)v, ww = (T)w;
     T Uc[3];
-    if constexpr (GEO == kMetricBox) {
-        Uc[0] = uu * mx[0];
-        Uc[1] = vv * mx[4];
-        Uc[2] = uu * mx[6] + vv * mx[7] + ww * mx[8];
-    } else {
-        Uc[0] = uu * mx[0] + vv * mx[1] + ww * mx[2];
-        Uc[1] = uu * mx[3] + vv * mx[4] + ww * mx[5];
-        Uc[2] = uu * mx[6] + vv * mx[7] + ww * mx[8];
-    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) Uc[d] = uu * mx[3 * d] + vv * mx[3 * d + 1] + ww * mx[3 * d + 2];
     // Cartesian derivative d/dx_c of field f (row c of the inverse metric)
-    auto cart = [&](int f, int c) -> T {
-        if constexpr (GEO == kMetricBox) {
-            if (c == 0) return dd[f][0] * mx[0] + dd[f][2] * mx[6];
-            if (c == 1) return dd[f][1] * mx[4] + dd[f][2] * mx[7];
-            return dd[f][2] * mx[8];
-        } else {
-            return dd[f][0] * mx[c] + dd[f][1] * mx[3 + c] + dd[f][2] * mx[6 + c];
-        }
-    };
+    auto cart = [&](int f, int c) -> T { return dd[f][0] * mx[c] + dd[f][1] * mx[3 + c] + dd[f][2] * mx[6 + c]; };
     auto adv = [&](int f) -> T { return Uc[0] * dd[f][0] + Uc[1] * dd[f][1] + Uc[2] * dd[f][2]; };
     const double irho64 = 1.0 / (rb + rp);
     const T irho = (T)irho64;
     const T buoy = (T)(rp * irho64);
-    T gx = 0, gy = 0, gz = (T)(-a.g0);
-    if constexpr (SHELL) {
-        gx = gv[0];
-        gy = gv[1];
-        gz = gv[2];
-    }
     o.R[0] = -(cart(0, 0) + cart(1, 1) + cart(2, 2));
-    o.R[1] = -adv(3) - cart(7, 0) * irho + buoy * gx;
-    o.R[2] = -adv(4) - cart(7, 1) * irho + buoy * gy;
-    o.R[3] = -adv(5) - cart(7, 2) * irho + buoy * gz;
-    o.R[4] = -adv(6);
-    if constexpr (SHELL) o.R[4] -= adv(8);
+    o.R[1] = -adv(3) - cart(7, 0) * irho + buoy * gv[0];
+    o.R[2] = -adv(4) - cart(7, 1) * irho + buoy * gv[1];
+    o.R[3] = -adv(5) - cart(7, 2) * irho + buoy * gv[2];
+    o.R[4] = -adv(6) - adv(8);
     o.Jw = mx[9];
 }
 
+// tile fields: 0 rho u, 1 rho v, 2 rho w, 3 u, 4 v, 5 w, 6 theta', 7 p' (8, shell: theta_bar)
 template <int N, typename T, bool SHELL, int GEO>
 __device__ __forceinline__ void node_derive(const RhsArgs<T> &a, int l, const NodeIn<T> &in, const T *Di,
                                             const T *Dj, const T *Dk, T (*s)[(N + 1) * (N + 1) * (N + 1)],
@@ -310,107 +368,44 @@ __device__ __forceinline__ void node_derive(const RhsArgs<T> &a, int l, const No
 {
     constexpr int P = N + 1, PP = P * P;
     const int i = l % P, j = (l / P) % P, k = l / PP;
-    T mx[10];
-    if constexpr (GEO == kMetricBox) {
-        box_node_metric<T>(a.bm, in.ez, in.zk, in.c0, in.c1, in.c2, in.c3, mx);
-    } else {  // stored, or the shell's recomputed metric (formed by node_gather)
+    // reference derivatives of field f
+    auto derive = [&](int f, T *d, bool xi, bool eta) {
+        d[0] = xi ? dot<P>(Di, [&](int m) { return s[f][m + P * (j + P * k)]; }) : T(0);
+        d[1] = eta ? dot<P>(Dj, [&](int m) { return s[f][i + P * (m + P * k)]; }) : T(0);
+        d[2] = dot<P>(Dk, [&](int m) { return s[f][i + P * (j + P * m)]; });
+    };
+    if constexpr (!SHELL) {
+#pragma clang fp contract(off)
+        T mx[10];
+        if constexpr (GEO == kMetricBox) {
+            box_node_metric<T>(a.bm, in.ez, in.zk, in.c0, in.c1, in.c2, in.c3, mx);
+        } else {  // stored
+            mx[0] = in.mx[0];
+            mx[4] = in.mx[4];
 #pragma unroll
-        for (int c = 0; c < 10; ++c) mx[c] = in.mx[c];
-    }
-    // reference derivatives of every field (the unused ones are dropped by
-    // the compiler), then R
-    constexpr int NF = SHELL ? 9 : 8;
-    T dd[NF][3];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-        T da = 0, db = 0, dc = 0;
-#pragma unroll
-        for (int m = 0; m < P; ++m) {
-            da += Di[m] * s[f][m + P * (j + P * k)];
-            db += Dj[m] * s[f][i + P * (m + P * k)];
-            dc += Dk[m] * s[f][i + P * (j + P * m)];
+            for (int c = 6; c < 10; ++c) mx[c] = in.mx[c];
         }
-        dd[f][0] = da;
-        dd[f][1] = db;
-        dd[f][2] = dc;
+        const double ird = 1.0 / (in.rb + in.rp);
+        T dd[5][3], fu[3], fv[3], fw[3];
+        derive(7, dd[0], true, true);
+#pragma unroll
+        for (int f = 1; f < 5; ++f) derive(2 + f, dd[f], true, true);
+        box_momentum<T>(mx, (T)in.u, (T)in.v, (T)in.w, dd, (T)ird, (T)(in.rp * ird), (T)(-a.g0), o.R + 1);
+        derive(0, fu, true, false);
+        derive(1, fv, false, true);
+        derive(2, fw, false, false);
+        const T dz[3] = {fu[2], fv[2], fw[2]};
+        o.R[0] = box_mass<T>(mx, fu[0], fv[1], dz);
+        o.Jw = mx[9];
+    } else {
+        T dd[9][3];
+#pragma unroll
+        for (int f = 0; f < 9; ++f) derive(f, dd[f], true, true);
+        T gv[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) gv[d] = GEO == kMetricShell ? in.gv[d] : (T)a.grav[d * a.nu + in.I];
+        shell_combine<T>(dd, in.mx, in.u, in.v, in.w, in.rp, in.rb, gv, o);
     }
-    T gv[3] = {0, 0, 0};
-    if constexpr (SHELL && GEO == kMetricShell) {
-        gv[0] = in.gv[0];
-        gv[1] = in.gv[1];
-        gv[2] = in.gv[2];
-    } else if constexpr (SHELL) {
-        gv[0] = (T)a.grav[in.I];
-        gv[1] = (T)a.grav[a.nu + in.I];
-        gv[2] = (T)a.grav[2 * a.nu + in.I];
-    }
-    node_combine<T, SHELL, GEO>(a, dd, mx, in.u, in.v, in.w, in.rp, in.rb, gv, o);
-}
-
-// node_derive for the box's recomputed metric with R accumulated direction
-// by direction: every term of R is linear in the reference derivatives, so
-// the xi terms of all fields are added first (row i of D), then the eta
-// terms (row j), then the zeta terms (row k).  One row of D and five sums
-// are live instead of three rows and 24 derivatives (the one-node-per-lane
-// kernel at 64x64x16: N = 7 1197 -> 1040 us, N = 8 2491 -> 2467 us; no gain
-// on the shell's or the stored metric's kernels, which keep node_derive).
-// The same terms as node_combine (GEO == kMetricBox), summed in another
-// order.
-template <int N, typename T>
-__device__ __forceinline__ void node_derive_box_dirs(const RhsArgs<T> &a, int l, const NodeIn<T> &in,
-                                                     T (*s)[(N + 1) * (N + 1) * (N + 1)], NodeOut<T> &o)
-{
-    constexpr int P = N + 1, PP = P * P;
-    const int i = l % P, j = (l / P) % P, k = l / PP;
-    T mx[10];
-    box_node_metric<T>(a.bm, in.ez, in.zk, in.c0, in.c1, in.c2, in.c3, mx);
-    const T uu = (T)in.u, vv = (T)in.v, ww = (T)in.w;
-    const T Uc0 = uu * mx[0], Uc1 = vv * mx[4], Uc2 = uu * mx[6] + vv * mx[7] + ww * mx[8];
-    const double irho64 = 1.0 / (in.rb + in.rp);
-    const T irho = (T)irho64;
-    // A: the sums whose negatives are R (tile fields: 0 rho u, 1 rho v,
-    // 2 rho w, 3 u, 4 v, 5 w, 6 theta', 7 p')
-    T A[5] = {0, 0, 0, 0, 0};
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int r = d == 0 ? i : (d == 1 ? j : k);
-        T Dr[P];
-#pragma unroll
-        for (int m = 0; m < P; ++m) Dr[m] = a.D[r * P + m];
-        auto dfd = [&](int f) -> T {
-            T acc = 0;
-#pragma unroll
-            for (int m = 0; m < P; ++m) {
-                const int at = d == 0 ? m + P * (j + P * k) : (d == 1 ? i + P * (m + P * k) : i + P * (j + P * m));
-                acc += Dr[m] * s[f][at];
-            }
-            return acc;
-        };
-        const T U = d == 0 ? Uc0 : (d == 1 ? Uc1 : Uc2);
-        // continuity: d(rho u)/dx = rho u_xi xi_x + rho u_zeta zeta_x, and so on
-        if (d == 0) A[0] += dfd(0) * mx[0];
-        if (d == 1) A[0] += dfd(1) * mx[4];
-        if (d == 2) A[0] += dfd(0) * mx[6] + dfd(1) * mx[7] + dfd(2) * mx[8];
-        // advection of u, v, w, theta'
-#pragma unroll
-        for (int f = 3; f < 7; ++f) A[f - 2] += U * dfd(f);
-        // pressure gradient over rho
-        const T dp = dfd(7);
-        if (d == 0) A[1] += irho * (dp * mx[0]);
-        if (d == 1) A[2] += irho * (dp * mx[4]);
-        if (d == 2) {
-            A[1] += irho * (dp * mx[6]);
-            A[2] += irho * (dp * mx[7]);
-            A[3] += irho * (dp * mx[8]);
-        }
-    }
-    const T buoy = (T)(in.rp * irho64);
-    o.R[0] = -A[0];
-    o.R[1] = -A[1];
-    o.R[2] = -A[2];
-    o.R[3] = -A[3] + buoy * (T)(-a.g0);
-    o.R[4] = -A[4];
-    o.Jw = mx[9];
 }
 
 // Gathers the element tile, differentiates it and evaluates R at node l of
@@ -551,6 +546,7 @@ __device__ __forceinline__ void box_finish_node(const PointArgs &p, const BoxFin
     int cx[2], cy[2], cz[2];
     int lx[2], ly[2], lz[2], nxc, nyc, nzc;
     const int exa = sx * SEG + a / N;
+    if (exa >= b.nx) return;  // past the row, in its last segment
     if (a % N == 0) {  // gi is a multiple of N: element face in x
         cx[0] = exa; lx[0] = 0;
         cx[1] = exa == 0 ? b.nx - 1 : exa - 1; lx[1] = N;
@@ -615,14 +611,11 @@ __device__ __forceinline__ void box_finish_node(const PointArgs &p, const BoxFin
                     for (int v = 0; v < 5; ++v) c[2 * y + x][v] = (T)0;
                 }
             }
+        // x pairs first, then over y and z, as the split DSS takes them
 #pragma unroll
         for (int y = 0; y < 2; ++y)
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const bool has = y < nyc && x < nxc;
-#pragma unroll
-                for (int v = 0; v < 5; ++v) r[v] += has ? (double)c[2 * y + x][v] : 0.0;
-            }
+            for (int v = 0; v < 5; ++v) r[v] += (double)(c[2 * y][v] + c[2 * y + 1][v]);
     }
 #pragma unroll
     for (int v = 0; v < 5; ++v) r[v] *= mi;

@@ -90,9 +90,6 @@ struct DeviceView {
     int32_t *shid = nullptr;   // shell: [6 ne^2][(N+1)^2] horizontal unique id of each element column
     int32_t *hoff = nullptr;   // shell: [n_horiz+1] offsets of the horizontal copy lists
     int32_t *hidx = nullptr;   // shell: [6 ne^2 (N+1)^2] copies e*np + l (bottom layer, k = 0), ascending
-    int32_t *own = nullptr;    // [n_unique] unique ids in first-occurrence order of the element scan
-    int32_t *toff = nullptr;   // [n_unique+1] copy offsets in that order
-    int32_t *tidx = nullptr;   // [n_local] copies (e*np + l), ascending per node, in that order
     double *ev64 = nullptr;    // [5][n_local] element contributions of a fused stage, FP64 path
     float *ev32 = nullptr;     // same, mixed path
     double *qs = nullptr;      // [5][n_unique] stage state scratch
@@ -114,7 +111,6 @@ struct Mesh {
     double xi[kMaxP]{}, w[kMaxP]{}, D[kMaxP * kMaxP]{};
     std::vector<int32_t> G, off, idx, hlat;
     std::vector<float> D32;
-    std::vector<int32_t> own, toff, tidx;
     std::vector<int32_t> hoff, hidx;  // shell: copies of each horizontal node in the bottom layer (e*np + l)
     // optional event timing of the stage kernels (numa_profile)
     bool profiling = false;
@@ -166,9 +162,7 @@ int32_t launch_geometry(Mesh &m, hipStream_t s);
 int32_t launch_export(Mesh &m, int32_t what, void *out, hipStream_t s);
 int32_t launch_init_state(Mesh &m, const numa_ic &ic, const double *noise, double *q, hipStream_t s);
 int32_t launch_rhs(Mesh &m, int32_t prec, const double *q, double *evec, hipStream_t s);
-// minv: the inverse mass applied with NUMA_DSS_MASS (null: the stored metric's M^-1)
-int32_t launch_dss(Mesh &m, int32_t nvar, const double *cin, double *out, int32_t flags, hipStream_t s,
-                   const double *minv = nullptr);
+int32_t launch_dss(Mesh &m, int32_t nvar, const double *cin, double *out, int32_t flags, hipStream_t s);
 void filter_sigma(int N, double order, int32_t cutoff, double *sigma);
 void filter_matrix(int N, const double *xi, const double *w, double order, int32_t cutoff, double *F);
 int32_t launch_filter(Mesh &m, double order, int32_t cutoff, double *q, hipStream_t s);
@@ -210,9 +204,10 @@ bool box_batchable(const Mesh &m);
 // the mesh's stages of precision prec run the split DSS (NUMA_STAGE_SPLIT,
 // or NUMA_STAGE_AUTO in FP64)
 bool split_ok(const Mesh &m, int32_t prec);
-// ... through the batched kernels: box_batchable, or the split DSS, which
-// takes any box x extent
-inline bool stage_batched(const Mesh &m, int32_t prec) { return box_batchable(m) || split_ok(m, prec); }
+// what numa_step_batch accepts: box_batchable, or the split DSS
+inline bool batch_accepts(const Mesh &m, int32_t prec) { return box_batchable(m) || split_ok(m, prec); }
+// the mesh's stages run through the batched kernels
+inline bool stage_batched(const Mesh &m) { return m.d.kind == NUMA_MESH_BOX; }
 int32_t launch_batch_stage(const StepItem *items, int n, int32_t prec, int phase, hipStream_t s);
 
 // Batched steps (api.cpp), shared by numa_step_batch and the no-allocation

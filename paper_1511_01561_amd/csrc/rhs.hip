@@ -160,16 +160,14 @@ int32_t launch_rhs(Mesh &m, int32_t prec, const double *q, double *evec, hipStre
     return NUMA_OK;
 }
 
-// element half of a fused stage: contributions into the workspace E-vector
-// (FP32 on the mixed path)
+// element half of a fused stage of the shell: node-major contributions into
+// the workspace E-vector (FP32 on the mixed path)
 int32_t launch_stage_elements(Mesh &m, int32_t prec, const StageCoef &c, const double *qs, hipStream_t s)
 {
-    // the shell's finish reads node-major contributions, the generic one element-major
-    const bool nm = m.d.kind == NUMA_MESH_SHELL;
     if (prec == NUMA_PREC_MIXED)
-        launch_t<float, float>(m, m.dv.met32, m.dv.D32, qs, m.dv.ev32, nm, s);
+        launch_t<float, float>(m, m.dv.met32, m.dv.D32, qs, m.dv.ev32, true, s);
     else
-        launch_t<double, double>(m, m.dv.met, m.dv.D64, qs, m.dv.ev64, nm, s, c.cdt, shell_folds(m, prec, c) ? 1 : 0);
+        launch_t<double, double>(m, m.dv.met, m.dv.D64, qs, m.dv.ev64, true, s, c.cdt, shell_folds(m, prec, c) ? 1 : 0);
     NUMA_HIP(hipGetLastError());
     return NUMA_OK;
 }
