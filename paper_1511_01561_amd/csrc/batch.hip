@@ -587,22 +587,24 @@ __global__ __launch_bounds__((col_threads<N, T>()), (col_blocks<N, T, MODE>())) 
 // values from the tile once per pass, the xi and eta rows per node.  Each term is
 // the product and sum of k_elem_col (in mixed precision the tile and the
 // contractions FP32, rho, 1/rho, rho'/rho and p' formed in FP64 as there);
-// the tail is the split DSS.  FP64: three workgroups per CU at N = 4 (50 KB
-// of LDS), four below (N = 3: 40 KB, a 16-byte stack frame, measured faster
-// than three without it); N = 5..8 as noted below.  Mixed (N <= 4): four
-// waves per SIMD.
+// the tail is the split DSS.  FP64: three workgroups per CU at N = 3, 4 (41 and
+// 50 KB of LDS; at N = 3 four would spill 48 bytes: 64x64x16 98 against 85 us),
+// four below; N = 5..8 as noted below.  Mixed (N <= 4): four waves per SIMD.
 template <int N, typename T> constexpr int col2_waves()
 {
     return sizeof(T) == 4 ? 4 : (N <= 2 ? 4 : (N <= 4 ? 3 : 2));
 }
 // doubles after each element's tile: at N = 4, 8 spread the xi and eta rows of
 // the two or three elements a wavefront spans over the LDS banks (50,640
-// bytes, still three workgroups per CU); at N = 3 the 40 KB tile has no room
+// bytes, still three workgroups per CU)
 template <int N, typename T = double> constexpr int col2_pad() { return sizeof(T) == 8 && N == 4 ? 8 : 0; }
-template <int N, typename T> constexpr int col2_group() { return N + 1; }
 // N = 5, 6 (seven and five elements per 256-lane workgroup, 60 and 69 KB of
 // LDS): two waves per SIMD
-template <int N, typename T = double>
+//
+// STORED: the metric is read instead of recomputed: the four entries of it
+// that vary on a box (zeta_x, zeta_y, zeta_z, J w), a node ahead of its use in
+// the first pass, J w and the others again (from the caches) in the second.
+template <int N, typename T = double, bool STORED = false>
 __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_elem_col2(Batch B)
 {
     constexpr bool F64 = sizeof(T) == 8;
@@ -627,6 +629,24 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
     T ir[P], bq[P];
     double c0 = 0.0, c1 = 0.0, c2 = 0.0, c3 = 0.0;
     int ez = 0;
+    // metric of the column's node k; stored: zeta_x, zeta_y, zeta_z, J w from mp
+    const T *mp = STORED ? a.met + ((int64_t)(act ? e0 + q : 0) * 10 + 6) * NP + c : nullptr;
+    T ahead[4];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) ahead[d] = mp[d * NP + PP * k];
+    };
+    auto metric = [&](int k, T *mx) {
+        if constexpr (STORED) {
+            mx[0] = (T)a.bm.ixa;
+            mx[4] = (T)a.bm.iyb;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) mx[6 + d] = ahead[d];
+            if (k < N) fetch(k + 1);
+        } else {
+            box_node_metric<T>(a.bm, ez, B.xi[k], c0 * B.w[k], c1, c2, c3, mx);
+        }
+    };
     T Di[P], Dj[P];
 #pragma unroll
     for (int m = 0; m < P; ++m) {
@@ -636,16 +656,18 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
     if (act) {
         const BoxElem be = box_elem((uint32_t)(e0 + q), a.fx, a.fy);
         ez = be.ez;
-        const double *cp = a.hcol + (int64_t)(be.ex + a.nx * be.ey) * (4 * PP) + c;
-        c0 = cp[0];
-        c1 = cp[PP];
-        c2 = cp[2 * PP];
-        c3 = cp[3 * PP];
+        if constexpr (!STORED) {
+            const double *cp = a.hcol + (int64_t)(be.ex + a.nx * be.ey) * (4 * PP) + c;
+            c0 = cp[0];
+            c1 = cp[PP];
+            c2 = cp[2 * PP];
+            c3 = cp[3 * PP];
+        }
         int gi = be.ex * N + i, gj = be.ey * N + j;
         if (gi == a.ni) gi = 0;
         if (gj == a.nj) gj = 0;
         const int base = gi + a.ni * gj, layer = a.ni * a.nj;
-        gather_column<P, col2_group<N, T>()>(a, it.theta0, base, layer, be.ez * N,
+        gather_column<P, P>(a, it.theta0, base, layer, be.ez * N,
                                              [&](int k, const double *qv, double rb, double pp) {
                                                  const int l = c + PP * k;
                                                  rho[k] = rb + qv[0];
@@ -661,13 +683,14 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
                                                  }
                                              });
     }
+    if (STORED && act) fetch(0);
     __syncthreads();  // first tile complete
     T res[P][5];
     if (act) {
 #pragma unroll
         for (int k = 0; k < P; ++k) {
             T mx[10];
-            box_node_metric<T>(a.bm, ez, B.xi[k], c0 * B.w[k], c1, c2, c3, mx);
+            metric(k, mx);
             const int l = c + PP * k;
             const T uu = S(q, 1, l), vv = S(q, 2, l), ww = S(q, 3, l), tt = S(q, 4, l);
             T dd[5][3];
@@ -712,12 +735,13 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
 #pragma unroll
             for (int f = 0; f < 2; ++f) S(q, f, c + PP * k) = fl[k][f];
     }
+    if (STORED && act) fetch(0);
     __syncthreads();  // second tile complete
     if (act) {
 #pragma unroll
         for (int k = 0; k < P; ++k) {
             T mx[10];
-            box_node_metric<T>(a.bm, ez, B.xi[k], c0 * B.w[k], c1, c2, c3, mx);
+            metric(k, mx);
             const T da = dot<P>(Di, [&](int m) { return S(q, 0, m + P * (j + P * k)); });
             const T db = dot<P>(Dj, [&](int m) { return S(q, 1, i + P * (m + P * k)); });
             T dz[3];
@@ -1118,6 +1142,7 @@ struct FilterSplit {
     BatchItem it;             // qs: the state read, qout: the state written (the same array)
     double w[kMaxP];          // GLL weights
     double F[kMaxP * kMaxP];  // 1D nodal filter matrix F[i * (N+1) + m]
+    const double *met;        // stored metric (J w is entry 9), or null: J w = c0 w_k
 };
 
 template <int N>
@@ -1150,7 +1175,10 @@ __global__ __launch_bounds__((split_threads<N>())) void k_filter_col(FilterSplit
     double jw[P];
     if (act) {
         const BoxElem be = box_elem((uint32_t)(e0 + q), it.fx, it.fy);
-        const double c0 = it.hcol[(int64_t)(be.ex + gm.nx * be.ey) * (4 * PP) + c];
+        const bool stored = A.met != nullptr;
+        const double *jp = stored ? A.met + ((int64_t)(e0 + q) * 10 + 9) * NP + c
+                                  : it.hcol + (int64_t)(be.ex + gm.nx * be.ey) * (4 * PP) + c;
+        const double c0 = stored ? 0.0 : jp[0];
         int gi = be.ex * N + i, gj = be.ey * N + j;
         if (gi == gm.ni) gi = 0;
         if (gj == gm.nj) gj = 0;
@@ -1162,7 +1190,7 @@ __global__ __launch_bounds__((split_threads<N>())) void k_filter_col(FilterSplit
             const int32_t I = base + layer * gk;
 #pragma unroll
             for (int v = 0; v < 5; ++v) S(q, v, c + PP * k) = it.qs[I + v * gm.nu];
-            jw[k] = c0 * A.w[k];
+            jw[k] = stored ? jp[PP * k] : c0 * A.w[k];
         }
     }
     __syncthreads();
@@ -1366,19 +1394,16 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
         }
     }
     if (split) {
-        if constexpr (kind == 0) {
-            if (phase == 0) {
-                hipLaunchKernelGGL((k_elem_col2<N, T>), dim3((unsigned)(eo / eb)), dim3(split_threads<N>()), 0, s, B);
+        constexpr bool f64 = std::is_same<T, double>::value;
+        if constexpr (kind == 0 || f64) {
+            const dim3 grid((unsigned)(eo / eb)), block(split_threads<N>());
+            if (phase == 1) {
+                hipLaunchKernelGGL((k_fin_split<N, T>), dim3((unsigned)bo), dim3(256), 0, s, B);
+            } else if (recompute) {
+                hipLaunchKernelGGL((k_elem_col2<N, T>), grid, block, 0, s, B);
             } else {
-                hipLaunchKernelGGL((k_fin_split<N, T>), dim3((unsigned)bo), dim3(256), 0, s, B);
+                if constexpr (f64) hipLaunchKernelGGL((k_elem_col2<N, T, true>), grid, block, 0, s, B);
             }
-            NUMA_HIP(hipGetLastError());
-            return NUMA_OK;
-        } else if constexpr (std::is_same<T, double>::value) {
-            if (phase == 0)
-                hipLaunchKernelGGL((k_elem_col2<N>), dim3((unsigned)(eo / eb)), dim3(split_threads<N>()), 0, s, B);
-            else
-                hipLaunchKernelGGL((k_fin_split<N, T>), dim3((unsigned)bo), dim3(256), 0, s, B);
             NUMA_HIP(hipGetLastError());
             return NUMA_OK;
         }
@@ -1576,6 +1601,7 @@ int32_t run_filter_split(const Mesh &m, const double *F, double *q, hipStream_t 
     const int64_t bo = split_item(m, EB, it);
     for (int k = 0; k <= N; ++k) A.w[k] = m.w[k];
     for (int k = 0; k < (N + 1) * (N + 1); ++k) A.F[k] = F[k];
+    A.met = m.metric_mode == NUMA_METRIC_RECOMPUTE ? nullptr : m.dv.met;
     hipLaunchKernelGGL((k_filter_col<N>), dim3((unsigned)((m.ne + EB - 1) / EB)), dim3(split_threads<N>()), 0, s, A);
     // the face nodes: the split finish with the identity update (a = b = 0, cdt = 1)
     Batch B{};
@@ -1619,16 +1645,14 @@ bool colour_ok(const Mesh &m)
            m.N <= 4 && m.d.ne[0] % 2 == 0 && m.d.ne[1] % 2 == 0 && m.d.ne[2] % 2 == 0;
 }
 
-// NUMA_STAGE_SPLIT runs a column element kernel (recomputed metric; N <= 4,
-// and in FP64 N = 5, 6 with the two-pass kernel); its finish takes any x
-// extent.  NUMA_STAGE_AUTO takes it in FP64 (measured faster than the gather
-// there; in mixed precision the gather, whose FP32 contributions are half the
-// bytes, is faster)
+// NUMA_STAGE_SPLIT runs the two-pass column element kernel (FP64: N <= 8 and
+// either metric; mixed precision: N <= 4, recomputed metric); its finish takes
+// any x extent.
 bool split_ok(const Mesh &m, int32_t prec)
 {
-    const bool mode = m.stage_mode == NUMA_STAGE_SPLIT || (m.stage_mode == NUMA_STAGE_AUTO && prec == NUMA_PREC_FP64);
-    const int nmax = prec == NUMA_PREC_FP64 ? 8 : 4;
-    return mode && m.d.kind == NUMA_MESH_BOX && m.metric_mode == NUMA_METRIC_RECOMPUTE && m.N <= nmax;
+    if (m.d.kind != NUMA_MESH_BOX) return false;
+    if (prec == NUMA_PREC_FP64) return m.stage_mode == NUMA_STAGE_SPLIT || m.stage_mode == NUMA_STAGE_AUTO;
+    return m.stage_mode == NUMA_STAGE_SPLIT && m.metric_mode == NUMA_METRIC_RECOMPUTE && m.N <= 4;
 }
 
 // NUMA_STAGE_AUTO: how a launch of nl element-local nodes in all runs a stage.
@@ -1660,6 +1684,19 @@ int auto_route(int N, int32_t prec, int64_t nl)
     return N <= 3 && nl < gather64[N] ? kGather : kSplit;
 }
 
+// With the stored metric the gather has one node per lane at every size (mixed
+// precision: always; FP64 against the split DSS).  us per step, node / split: 1:
+// 33 k 32 / 44, 131 k 55 / 45; 2: 221 k 54 / 62, 885 k 137 / 110; 3: 262 k 55 / 55,
+// 786 k 98 / 91; 4: 1.02 M 131 / 134, 1.28 M 154 / 143, 8.2 M 1,165 / 961; 5: 1.3 M
+// 172 / 181, 1.8 M 237 / 232; 6: 527 k 118 / 124, 702 k 147 / 130; 7: 655 k 120 / 134,
+// 918 k 153 / 145; 8: 560 k 134 / 156, 746 k 173 / 165.
+int auto_route_stored(int N, int32_t prec, int64_t nl)
+{
+    //                                     N = 1      2       3        4        5       6        7        8
+    static const int64_t node64[9] = {0, 80000, 350000, 300000, 1050000, 1600000, 570000, 850000, 650000};
+    return prec == NUMA_PREC_MIXED || nl < node64[N] ? kNode : kSplit;
+}
+
 int32_t launch_batch_stage(const StepItem *items, int n, int32_t prec, int phase, hipStream_t s)
 {
     // items the fused block kernels take (pencil.hip), the colour passes, the
@@ -1679,7 +1716,7 @@ int32_t launch_batch_stage(const StepItem *items, int n, int32_t prec, int phase
             const int g = pencil_stage_ok(items[k], prec)       ? 4
                           : colour_ok(m)                        ? kColour
                           : m.stage_mode != NUMA_STAGE_AUTO     ? (split_ok(m, prec) ? kSplit : kGather)
-                          : m.metric_mode == NUMA_METRIC_STORED ? kNode
+                          : m.metric_mode == NUMA_METRIC_STORED ? auto_route_stored(m.N, prec, nl)
                                                                 : auto_route(m.N, prec, nl);
             part[g][cnt[g]++] = items[k];
         }

@@ -204,8 +204,12 @@ bool box_batchable(const Mesh &m);
 // the mesh's stages of precision prec run the split DSS (NUMA_STAGE_SPLIT,
 // or NUMA_STAGE_AUTO in FP64)
 bool split_ok(const Mesh &m, int32_t prec);
-// what numa_step_batch accepts: box_batchable, or the split DSS
-inline bool batch_accepts(const Mesh &m, int32_t prec) { return box_batchable(m) || split_ok(m, prec); }
+// what numa_step_batch accepts: box_batchable, or the split DSS with the
+// recomputed metric
+inline bool batch_accepts(const Mesh &m, int32_t prec)
+{
+    return box_batchable(m) || (split_ok(m, prec) && m.metric_mode == NUMA_METRIC_RECOMPUTE);
+}
 // the mesh's stages run through the batched kernels
 inline bool stage_batched(const Mesh &m) { return m.d.kind == NUMA_MESH_BOX; }
 int32_t launch_batch_stage(const StepItem *items, int n, int32_t prec, int phase, hipStream_t s);

@@ -26,12 +26,13 @@ def _pair(N, ne, perz, oracle_mod):
     return Pair(wl, oracle_mod)
 
 
+@pytest.mark.parametrize("metric", ["stored", "recompute"])
 @pytest.mark.parametrize("N,ne,perz", CASES)
-def test_routes_agree(torch_cuda, oracle_mod, N, ne, perz):
+def test_routes_agree(torch_cuda, oracle_mod, N, ne, perz, metric):
     import torch
     from paper_1511_01561_amd import numa
     p = _pair(N, ne, perz, oracle_mod)
-    p.g.set_metric(numa.METRIC_RECOMPUTE)
+    p.g.set_metric(numa.METRIC_RECOMPUTE if metric == "recompute" else numa.METRIC_STORED)
     q = inputs.random_state(p.nu, seed=300 + N, rho_scale=0.04)
     assert (abs(q[0]) > 0.02).any()  # beyond the series with rho_bar of order one
     Ro = p.o.dss(p.o.rhs(q), 3)
@@ -50,12 +51,13 @@ def test_routes_agree(torch_cuda, oracle_mod, N, ne, perz):
                 assert torch.equal(a, b), (prec, mode)
 
 
+@pytest.mark.parametrize("metric", [0, 1])
 @pytest.mark.parametrize("N,ne", [(3, (5, 3, 2)), (4, (3, 3, 3)), (6, (7, 2, 2))])
-def test_filter_routes_agree(torch_cuda, oracle_mod, N, ne):
+def test_filter_routes_agree(torch_cuda, oracle_mod, N, ne, metric):
     import torch
     from paper_1511_01561_amd import numa
     p = _pair(N, ne, False, oracle_mod)
-    p.g.set_metric(numa.METRIC_RECOMPUTE)
+    p.g.set_metric(metric)
     q = inputs.random_state(p.nu, seed=320 + N)
     out = []
     for mode in (numa.STAGE_AUTO, numa.STAGE_SPLIT):
