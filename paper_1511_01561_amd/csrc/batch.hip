@@ -175,21 +175,17 @@ __global__ __launch_bounds__(block_threads<N>(), N == 8 && sizeof(T) == 4 ? 6 : 
     if (act) d_rows<N, T>(a.D, l, Di, Dj, Dk);  // in flight with the gather
     node_stage<N, T, false, GEO>(a, e, l, in, s);
     __syncthreads();
-    if (act) node_derive<N, T, false, GEO>(a, l, in, Di, Dj, Dk, s, o);
-    __syncthreads();  // every lane has finished reading the tile
-    T *st = &s[0][0];
     if (act) {
         const int k = l / ((N + 1) * (N + 1));
         const bool wall = it.walls && ((in.ez == 0 && k == 0) || (in.ez == it.nz - 1 && k == N));
-        if (sizeof(T) == 8 && B.fold && !wall) {  // J w (q_s + cdt R), as in k_elem_col
-            const double qv[5] = {in.rp, in.u, in.v, in.w, in.tp};
-#pragma unroll
-            for (int v = 0; v < 5; ++v) st[l * 5 + v] = o.Jw * fma((T)it.cdt, o.R[v], (T)qv[v]);
-        } else {
-#pragma unroll
-            for (int v = 0; v < 5; ++v) st[l * 5 + v] = o.Jw * o.R[v];
-        }
+        const bool fold = sizeof(T) == 8 && B.fold && !wall;
+        node_derive<N, T, false, GEO>(a, l, in, Di, Dj, Dk, s, o, {fold ? (T)it.cdt : T(1), fold});
     }
+    __syncthreads();  // every lane has finished reading the tile
+    T *st = &s[0][0];
+    if (act)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) st[l * 5 + v] = o.Jw * o.R[v];
     __syncthreads();
     store_contributions<N, T>(it, e, l, st);
 }
@@ -525,26 +521,27 @@ __global__ __launch_bounds__((col_threads<N, T>()), (col_blocks<N, T, MODE>())) 
             const int l = c + PP * k;
             const T uu = s[q][3][l], vv = s[q][4][l], ww = s[q][5][l];
             const T bk = F64 ? buoy[k] * irho[k] : buoy[k];
-            T R[5], dm[5][3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                dm[0][d] = dd[7][d];
-#pragma unroll
-                for (int f = 1; f < 5; ++f) dm[f][d] = dd[2 + f][d];
-            }
-            box_momentum<T>(mx, uu, vv, ww, dm, irho[k], bk, (T)(-a.g0), R + 1);
-            const T dzm[3] = {dd[0][2], dd[1][2], dd[2][2]};
-            R[0] = box_mass<T>(mx, dd[0][0], dd[1][1], dzm);
             // J w R, or J w (q_s + cdt R) away from the walls when folding
             const bool wall = it.walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
-            if (F64 && B.fold && !wall) {
-                const T qv[5] = {buoy[k], uu, vv, ww, s[q][6][l]};
+            const bool fold = F64 && B.fold && !wall;
+            T U[3], pr[3];
+            box_velocity<T>(mx, uu, vv, ww, U);
+            box_pressure<T>(mx, dd[7], irho[k], bk, (T)(-a.g0), pr);
+            const T qv[4] = {uu, vv, ww, s[q][6][l]}, dzm[3] = {dd[0][2], dd[1][2], dd[2][2]};
+            // a branch, not a select: it keeps a node's values apart from the next one's
+            auto terms = [&](const FoldTerms<T> ft) {
 #pragma unroll
-                for (int v = 0; v < 5; ++v) res[k][v] = mx[9] * fma((T)it.cdt, R[v], qv[v]);
-            } else {
-#pragma unroll
-                for (int v = 0; v < 5; ++v) res[k][v] = mx[9] * R[v];
-            }
+                for (int f = 0; f < 4; ++f) {
+                    T r = fm(-ft.s, box_advect<T>(U, dd[3 + f]), ft.base(qv[f]));
+                    if (f < 3) r = fm(ft.s, pr[f], r);
+                    res[k][1 + f] = mx[9] * r;
+                }
+                res[k][0] = mx[9] * fm(ft.s, box_mass<T>(mx, dd[0][0], dd[1][1], dzm), ft.base(buoy[k]));
+            };
+            if (fold)
+                terms({(T)it.cdt, true});
+            else
+                terms({T(1), false});
         }
     }
     if constexpr (MODE == 1) {
@@ -702,17 +699,19 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
             }
             if constexpr (F64) ir[k] = (T)(1.0 / rho[k]);
             const T bk = F64 ? bq[k] * ir[k] : bq[k];
-            T R[4];
-            box_momentum<T>(mx, uu, vv, ww, dd, ir[k], bk, (T)gz, R);
             const bool wall = walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
-            if (fold && !wall) {
-                const T qv[4] = {uu, vv, ww, tt};
+            const FoldTerms<T> ft{fold && !wall ? (T)cdt : T(1), fold && !wall};
+            T U[3], pr[3];
+            box_velocity<T>(mx, uu, vv, ww, U);
+            box_pressure<T>(mx, dd[0], ir[k], bk, (T)gz, pr);
+            const T qv[4] = {uu, vv, ww, tt};
 #pragma unroll
-                for (int v = 0; v < 4; ++v) res[k][v + 1] = mx[9] * fma((T)cdt, R[v], qv[v]);
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) res[k][v + 1] = mx[9] * R[v];
+            for (int f = 0; f < 4; ++f) {
+                T r = fm(-ft.s, box_advect<T>(U, dd[1 + f]), ft.base(qv[f]));
+                if (f < 3) r = fm(ft.s, pr[f], r);
+                res[k][1 + f] = mx[9] * r;
             }
+            __builtin_amdgcn_sched_barrier(0);  // a node's rows at a time: registers
         }
     }
     // the mass fluxes of the column, formed from the first tile: rho u and
@@ -747,9 +746,9 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
             T dz[3];
 #pragma unroll
             for (int f = 0; f < 3; ++f) dz[f] = dot<P>(a.D + k * P, [&](int m) { return fl[m][f]; });
-            const T R0 = box_mass<T>(mx, da, db, dz);
             const bool wall = walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
-            res[k][0] = (fold && !wall) ? mx[9] * fma((T)cdt, R0, bq[k]) : mx[9] * R0;
+            const FoldTerms<T> ft{fold && !wall ? (T)cdt : T(1), fold && !wall};
+            res[k][0] = mx[9] * fm(ft.s, box_mass<T>(mx, da, db, dz), ft.base(bq[k]));
         }
     }
     // the run-interior nodes' M^-1 and q^n (issued here, where the tiles'
@@ -758,6 +757,220 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
     split_prefetch<N, EB, BT>(it, gm, B.ca != 0.0, t, e0, new_, pf);
     __syncthreads();  // second tile read
     T *st = &s[0][0];
+    if (act) {
+#pragma unroll
+        for (int k = 0; k < P; ++k)
+#pragma unroll
+            for (int v = 0; v < 5; ++v) st[(q * NP + c + PP * k) * 5 + v] = res[k][v];
+    }
+    __syncthreads();
+    split_store<N, T, EB, BT>(it, gm, StageCoef{B.ca, B.cb, cdt}, fold, st, t, e0, new_, pf);
+}
+
+// The element kernel of the split DSS in FP64 with derivatives by rows.  In
+// k_elem_col2 a lane reads, for each of its nodes and fields, the N+1 values of
+// the xi and of the eta line through the node, each for one multiply-add: the
+// LDS is busy 53-65 % of the time and the chain of reads is what a wavefront
+// waits for.  Here the lanes also take the lines themselves: lane (a, b) of an
+// element reads the xi line (j, k) = (a, b) and the eta line (i, k) = (a, b) of a
+// field once, forms all N+1 derivatives of each (rows of D are lane-uniform:
+// scalar operands) and writes them back, the xi derivatives over the field, the
+// eta derivatives to a spare slot, from where the column lanes read theirs:
+// about 7 LDS accesses per node and field instead of 2 N + 3.  A field costs two
+// barriers (its lines are read; its derivatives are written).  The mass
+// fluxes go first (xi of rho u, eta of rho v), then theta', w, v, u and last p',
+// each from the slot it was stored in at the gather (p' from the lane's
+// registers).  Each operation is that of the other box kernels.
+// Rows are padded to an odd length (line lanes then fall on distinct banks).
+// Taken at N = 5, 6 (two waves per SIMD): 32x32x16 113 -> 106 us and 207 -> 186
+// us against k_elem_col2.  At N <= 4 the barriers cost what the reads save
+// (64x64x16, N = 4: 207 against 211 us, N = 3: 90 against 85), at N = 7, 8 the
+// padded tile and the registers leave one wave per SIMD or spill (418 against
+// 301 us, 354 against 293).  Two lanes per column (half the registers, twice the
+// waves) measured 110 us at N = 5, 279 at N = 6, 503 at N = 8.
+template <int N> constexpr bool rows_ok() { return N == 5 || N == 6; }
+template <int N> constexpr int row_len() { return (N + 1) | 1; }
+template <int N> constexpr int rows_slot() { return (N + 1) * (N + 1) * row_len<N>(); }
+template <int N, bool STORED>
+__global__ __launch_bounds__((split_threads<N>()), 2) void k_elem_rows(Batch B)
+{
+    using T = double;
+    constexpr int P = N + 1, PP = P * P, NP = PP * P, EB = split_eb<N>(), BT = split_threads<N>();
+    constexpr int RS = row_len<N>(), NS = rows_slot<N>(), RP = RS * P;
+    __shared__ double s[EB][5 * NS];
+    const int g0 = (int)xcd_remap(blockIdx.x, gridDim.x) * EB;
+    const BatchItem &it = B.it[batch_item(B, g0, false)];
+    const RhsArgs<T> a = elem_args<T>(B, it);
+    const int e0 = g0 - it.eoff;
+    const int t = threadIdx.x, q = t / PP, c = t % PP, i = c % P, j = c / P;
+    const bool act = q < EB && e0 + q < it.ne;
+    const int new_ = it.ne - e0 < EB ? it.ne - e0 : EB;
+    const SplitGeo gm{a.nx, a.ny, a.nz, a.ni, a.nj, (int)a.nu, a.fx, a.fy};
+    const bool fold = B.fold != 0;
+    const double cdt = it.cdt, gz = -a.g0;
+    // slot f of the lane's element; node k of its column, entry m of its xi
+    // and of its eta line
+    double *S = &s[act ? q : 0][0];
+    const int col = i + RS * j;
+    auto node = [&](int f, int k) -> double & { return S[f * NS + col + RP * k]; };
+    auto xi = [&](int f, int m) -> double & { return S[f * NS + RS * c + m]; };
+    auto eta = [&](int f, int m) -> double & { return S[f * NS + i + RS * m + RP * j]; };
+    constexpr int SU = 0, SV = 1, SW = 2, ST = 3, SE = 4;  // u, v, w, theta' (p' later), spare
+    double c0 = 0.0, c1 = 0.0, c2 = 0.0, c3 = 0.0;
+    int ez = 0;
+    const double *mp = STORED ? a.met + ((int64_t)(act ? e0 + q : 0) * 10 + 6) * NP + c : nullptr;
+    double ahead[4];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) ahead[d] = mp[d * NP + PP * k];
+    };
+    auto metric = [&](int k, double *mx) {
+        if constexpr (STORED) {
+            mx[0] = a.bm.ixa;
+            mx[4] = a.bm.iyb;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) mx[6 + d] = ahead[d];
+            fetch(k < N ? k + 1 : 0);
+        } else {
+            box_node_metric<T>(a.bm, ez, B.xi[k], c0 * B.w[k], c1, c2, c3, mx);
+        }
+    };
+    double rho[P], bq[P], pp[P], uv[2][P], res[P][5];
+    if (act) {
+        const BoxElem be = box_elem((uint32_t)(e0 + q), a.fx, a.fy);
+        ez = be.ez;
+        if constexpr (!STORED) {
+            const double *cp = a.hcol + (int64_t)(be.ex + a.nx * be.ey) * (4 * PP) + c;
+            c0 = cp[0];
+            c1 = cp[PP];
+            c2 = cp[2 * PP];
+            c3 = cp[3 * PP];
+        }
+        int gi = be.ex * N + i, gj = be.ey * N + j;
+        if (gi == a.ni) gi = 0;
+        if (gj == a.nj) gj = 0;
+        const int base = gi + a.ni * gj, layer = a.ni * a.nj;
+        gather_column<P, P>(a, it.theta0, base, layer, be.ez * N,
+                            [&](int k, const double *qv, double rb, double p) {
+                                rho[k] = rb + qv[0];
+                                bq[k] = qv[0];
+                                pp[k] = p;
+                                uv[0][k] = qv[1];
+                                uv[1][k] = qv[2];
+                                node(SU, k) = rho[k] * qv[1];
+                                node(SV, k) = rho[k] * qv[2];
+                                node(SW, k) = qv[3];
+                                node(ST, k) = qv[4];
+                            });
+        if constexpr (STORED) fetch(0);
+    }
+    // where node k folds q_s in: FoldTerms
+    auto terms = [&](int k) -> FoldTerms<T> {
+        const bool wall = it.walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
+        return {fold && !wall ? cdt : 1.0, fold && !wall};
+    };
+    double dx[P], de[P];
+    auto line = [&](auto at, int f, double *d) {
+        double r[P];
+#pragma unroll
+        for (int m = 0; m < P; ++m) r[m] = at(f, m);
+#pragma unroll
+        for (int n = 0; n < P; ++n) d[n] = dot<P>(a.D + n * P, [&](int m) { return r[m]; });
+    };
+    __syncthreads();
+    // mass row
+    double U[P][3];
+    {
+        double dz[3][P];
+        if (act) {
+            line(xi, SU, dx);
+            line(eta, SV, de);
+#pragma unroll
+            for (int f = 0; f < 3; ++f) {
+                double fl[P];
+#pragma unroll
+                for (int m = 0; m < P; ++m) fl[m] = f < 2 ? node(f, m) : rho[m] * node(SW, m);
+#pragma unroll
+                for (int k = 0; k < P; ++k) dz[f][k] = dot<P>(a.D + k * P, [&](int m) { return fl[m]; });
+            }
+        }
+        __syncthreads();
+        if (act)
+#pragma unroll
+            for (int m = 0; m < P; ++m) {
+                xi(SU, m) = dx[m];
+                eta(SV, m) = de[m];
+            }
+        __syncthreads();
+        if (act)
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                double mx[10];
+                metric(k, mx);
+                const double dk[3] = {dz[0][k], dz[1][k], dz[2][k]};
+                const FoldTerms<T> ft = terms(k);
+                res[k][0] = mx[9] * fm(ft.s, box_mass<T>(mx, node(SU, k), node(SV, k), dk), ft.base(bq[k]));
+                box_velocity<T>(mx, uv[0][k], uv[1][k], node(SW, k), U[k]);
+            }
+    }
+    __syncthreads();
+    if (act)
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            node(SU, k) = uv[0][k];
+            node(SV, k) = uv[1][k];
+        }
+    // theta', w, v, u, then p' from theta''s slot, free by then; u and v are
+    // stored two barriers before their lines are read
+#pragma unroll
+    for (int step = 0; step < 5; ++step) {
+        const int f = step == 4 ? ST : ST - step;
+        double cf[P], d2[P];
+        if (act) {
+            line(xi, f, dx);
+            line(eta, f, de);
+#pragma unroll
+            for (int m = 0; m < P; ++m) cf[m] = node(f, m);
+#pragma unroll
+            for (int k = 0; k < P; ++k) d2[k] = dot<P>(a.D + k * P, [&](int m) { return cf[m]; });
+        }
+        __syncthreads();
+        if (act) {
+#pragma unroll
+            for (int m = 0; m < P; ++m) {
+                xi(f, m) = dx[m];
+                eta(SE, m) = de[m];
+            }
+            if (step == 3)
+#pragma unroll
+                for (int k = 0; k < P; ++k) node(ST, k) = pp[k];
+        }
+        __syncthreads();
+        if (act)
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const double d[3] = {node(f, k), node(SE, k), d2[k]};
+                const FoldTerms<T> ft = terms(k);
+                if (step < 4) {
+                    const double r = fm(-ft.s, box_advect<T>(U[k], d), ft.base(cf[k]));
+                    res[k][1 + f] = r;
+                } else {
+                    double mx[10], pr[3];
+                    metric(k, mx);
+                    const double ir = 1.0 / rho[k];
+                    box_pressure<T>(mx, d, ir, bq[k] * ir, gz, pr);
+#pragma unroll
+                    for (int v = 0; v < 3; ++v) res[k][1 + v] = mx[9] * fm(ft.s, pr[v], res[k][1 + v]);
+                    res[k][4] = mx[9] * res[k][4];
+                }
+            }
+    }
+    // the run-interior nodes' M^-1 and q^n (issued here, where the tiles'
+    // registers are free)
+    SplitPre<N, EB, BT> pf;
+    split_prefetch<N, EB, BT>(it, gm, B.ca != 0.0, t, e0, new_, pf);
+    __syncthreads();  // the last derivatives are read
+    double *st = &s[0][0];
     if (act) {
 #pragma unroll
         for (int k = 0; k < P; ++k)
@@ -1095,15 +1308,22 @@ __global__ __launch_bounds__((col_threads<N, T>())) void k_elem_stream(Batch B)
                 const T dc = dot<P>(D + k * P, [&](int m) { return cf[m]; });
                 if (f != 1 && f != 2) da = dot<P>(Di, [&](int m) { return s[q][f][m + P * (j + P * k)]; });
                 if (f != 0 && f != 2) db = dot<P>(Dj, [&](int m) { return s[q][f][i + P * (m + P * k)]; });
-                // the operations of box_mass and box_momentum, a field at a time
+                // the operations of box_mass, box_advect and box_pressure, a field at a time
                 if (f == 0) R[k][0] = fm(dc, mx6, da * mx0);              // d(rho u)/dx
                 if (f == 1) R[k][0] = R[k][0] + fm(dc, mx7, db * mx4);    // + d(rho v)/dy
                 if (f == 2) R[k][0] = -fm(dc, mx8, R[k][0]);              // + d(rho w)/dz
-                if (f >= 3 && f <= 6) R[k][f - 2] = -fm(Uc[k][2], dc, fm(Uc[k][1], db, Uc[k][0] * da));
+                const T dd[3] = {da, db, dc};
+                if (f >= 3 && f <= 6) R[k][f - 2] = -box_advect<T>(Uc[k], dd);
                 if (f == 7) {
-                    R[k][1] = fm(-fm(dc, mx6, da * mx0), irho[k], R[k][1]);
-                    R[k][2] = fm(-fm(dc, mx7, db * mx4), irho[k], R[k][2]);
-                    R[k][3] = fm(buoy[k], (T)(-a.g0), fm(-(dc * mx8), irho[k], R[k][3]));
+                    T mx[10], pr[3];
+                    mx[0] = mx0;
+                    mx[4] = mx4;
+                    mx[6] = mx6;
+                    mx[7] = mx7;
+                    mx[8] = mx8;
+                    box_pressure<T>(mx, dd, irho[k], buoy[k], (T)(-a.g0), pr);
+#pragma unroll
+                    for (int v = 0; v < 3; ++v) R[k][1 + v] = pr[v] + R[k][1 + v];
                 }
             }
         }
@@ -1399,6 +1619,11 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
             const dim3 grid((unsigned)(eo / eb)), block(split_threads<N>());
             if (phase == 1) {
                 hipLaunchKernelGGL((k_fin_split<N, T>), dim3((unsigned)bo), dim3(256), 0, s, B);
+            } else if constexpr (f64 && rows_ok<N>()) {
+                if (recompute)
+                    hipLaunchKernelGGL((k_elem_rows<N, false>), grid, block, 0, s, B);
+                else
+                    hipLaunchKernelGGL((k_elem_rows<N, true>), grid, block, 0, s, B);
             } else if (recompute) {
                 hipLaunchKernelGGL((k_elem_col2<N, T>), grid, block, 0, s, B);
             } else {
@@ -1676,7 +1901,7 @@ bool split_ok(const Mesh &m, int32_t prec)
 int auto_route(int N, int32_t prec, int64_t nl)
 {
     //                                     N = 1      2       3        4        5       6        7        8
-    static const int64_t node64[9] = {0, 28000, 95000, 200000, 1050000, 2000000, 570000, 850000, 620000};
+    static const int64_t node64[9] = {0, 28000, 95000, 200000, 600000, 1500000, 500000, 720000, 600000};
     static const int64_t gather64[4] = {0, 800000, 2300000, 620000};
     static const int64_t nodemx[9] = {0, 28000, 90000, 190000, 400000, 1000000, 450000, 2300000, 1800000};
     if (prec == NUMA_PREC_MIXED) return nl < nodemx[N] ? kNode : kGather;
@@ -1693,7 +1918,7 @@ int auto_route(int N, int32_t prec, int64_t nl)
 int auto_route_stored(int N, int32_t prec, int64_t nl)
 {
     //                                     N = 1      2       3        4        5       6        7        8
-    static const int64_t node64[9] = {0, 80000, 350000, 300000, 1050000, 1600000, 570000, 850000, 650000};
+    static const int64_t node64[9] = {0, 80000, 300000, 280000, 600000, 1300000, 500000, 720000, 600000};
     return prec == NUMA_PREC_MIXED || nl < node64[N] ? kNode : kSplit;
 }
 

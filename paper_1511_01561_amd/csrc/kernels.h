@@ -91,21 +91,43 @@ __device__ __forceinline__ void eos_nodes(int n, const double *x, const double *
             if (k < n && !eos_small(x[k])) pp[k] = pb[k] * eos_rel_large(x[k], gamma);
 }
 
-// the momentum and theta' rows of R (R_u, R_v, R_w, R_theta') from the
-// reference derivatives dd of p', u, v, w, theta': advection in contravariant
-// form (u . grad f = sum_d U_d df/dxi_d), pressure gradient, buoyancy.  mx:
-// xi_x (0), eta_y (4), zeta_x, zeta_y, zeta_z (6..8); bk = rho'/rho
+// mx: xi_x (0), eta_y (4), zeta_x, zeta_y, zeta_z (6..8), J w (9).
+// contravariant velocity U_d = u . grad(xi_d), and u . grad f = sum_d U_d df/dxi_d
 template <typename T>
-__device__ __forceinline__ void box_momentum(const T *mx, T uu, T vv, T ww, const T (*dd)[3], T ir, T bk, T gz, T *R)
+__device__ __forceinline__ void box_velocity(const T *mx, T u, T v, T w, T *U)
 {
 #pragma clang fp contract(off)
-    const T U0 = uu * mx[0], U1 = vv * mx[4], U2 = fm(ww, mx[8], fm(vv, mx[7], uu * mx[6]));
-    auto adv = [&](int f) -> T { return fm(U2, dd[f][2], fm(U1, dd[f][1], U0 * dd[f][0])); };
-    R[0] = -fm(fm(dd[0][2], mx[6], dd[0][0] * mx[0]), ir, adv(1));
-    R[1] = -fm(fm(dd[0][2], mx[7], dd[0][1] * mx[4]), ir, adv(2));
-    R[2] = fm(bk, gz, -fm(dd[0][2] * mx[8], ir, adv(3)));
-    R[3] = -adv(4);
+    U[0] = u * mx[0];
+    U[1] = v * mx[4];
+    U[2] = fm(w, mx[8], fm(v, mx[7], u * mx[6]));
 }
+template <typename T>
+__device__ __forceinline__ T box_advect(const T *U, const T *d)
+{
+#pragma clang fp contract(off)
+    return fm(U[2], d[2], fm(U[1], d[1], U[0] * d[0]));
+}
+
+// pressure gradient and buoyancy of the momentum rows from the reference
+// derivatives of p' (dp), 1/rho and bk = rho'/rho
+template <typename T>
+__device__ __forceinline__ void box_pressure(const T *mx, const T *dp, T ir, T bk, T gz, T *R)
+{
+#pragma clang fp contract(off)
+    R[0] = -(fm(dp[2], mx[6], dp[0] * mx[0]) * ir);
+    R[1] = -(fm(dp[2], mx[7], dp[1] * mx[4]) * ir);
+    R[2] = fm(bk, gz, -(dp[2] * mx[8] * ir));
+}
+
+// The value a node contributes, before J w: b + s R with (s, b) = (cdt, q_s) where
+// the stage state is folded in, else (1, 0); R a sum of terms added one after
+// another (the advection's first): fm(s, term, b)
+template <typename T>
+struct FoldTerms {
+    T s;
+    bool on;
+    __device__ __forceinline__ T base(T q) const { return on ? q : T(0); }
+};
 
 // the mass row: da = d(rho u)/dxi, db = d(rho v)/deta, dz = d(rho u, rho v, rho w)/dzeta
 template <typename T>
@@ -184,7 +206,7 @@ __device__ __forceinline__ int32_t box_unique(const RhsArgs<T> &a, const BoxElem
 template <int N>
 constexpr int block_threads() { return (((N + 1) * (N + 1) * (N + 1) + 63) / 64) * 64; }
 
-// Per-node result of the element RHS.
+// Per-node result of the element RHS (on the box b + s R, FoldTerms).
 template <typename T>
 struct NodeOut {
     T R[5];  // R_rho', R_u, R_v, R_w, R_theta'
@@ -364,7 +386,7 @@ __device__ __forceinline__ void shell_combine(const T (*dd)[3], const T *mx, dou
 template <int N, typename T, bool SHELL, int GEO>
 __device__ __forceinline__ void node_derive(const RhsArgs<T> &a, int l, const NodeIn<T> &in, const T *Di,
                                             const T *Dj, const T *Dk, T (*s)[(N + 1) * (N + 1) * (N + 1)],
-                                            NodeOut<T> &o)
+                                            NodeOut<T> &o, FoldTerms<T> fold = {T(1), false})
 {
     constexpr int P = N + 1, PP = P * P;
     const int i = l % P, j = (l / P) % P, k = l / PP;
@@ -386,16 +408,23 @@ __device__ __forceinline__ void node_derive(const RhsArgs<T> &a, int l, const No
             for (int c = 6; c < 10; ++c) mx[c] = in.mx[c];
         }
         const double ird = 1.0 / (in.rb + in.rp);
-        T dd[5][3], fu[3], fv[3], fw[3];
-        derive(7, dd[0], true, true);
+        T U[3], d[3], pr[3], fu[3], fv[3], fw[3];
+        box_velocity<T>(mx, (T)in.u, (T)in.v, (T)in.w, U);
+        const T q[4] = {(T)in.u, (T)in.v, (T)in.w, (T)in.tp};
 #pragma unroll
-        for (int f = 1; f < 5; ++f) derive(2 + f, dd[f], true, true);
-        box_momentum<T>(mx, (T)in.u, (T)in.v, (T)in.w, dd, (T)ird, (T)(in.rp * ird), (T)(-a.g0), o.R + 1);
+        for (int f = 0; f < 4; ++f) {
+            derive(3 + f, d, true, true);
+            o.R[1 + f] = fm(-fold.s, box_advect<T>(U, d), fold.base(q[f]));
+        }
+        derive(7, d, true, true);
+        box_pressure<T>(mx, d, (T)ird, (T)(in.rp * ird), (T)(-a.g0), pr);
+#pragma unroll
+        for (int f = 0; f < 3; ++f) o.R[1 + f] = fm(fold.s, pr[f], o.R[1 + f]);
         derive(0, fu, true, false);
         derive(1, fv, false, true);
         derive(2, fw, false, false);
         const T dz[3] = {fu[2], fv[2], fw[2]};
-        o.R[0] = box_mass<T>(mx, fu[0], fv[1], dz);
+        o.R[0] = fm(fold.s, box_mass<T>(mx, fu[0], fv[1], dz), fold.base((T)in.rp));
         o.Jw = mx[9];
     } else {
         T dd[9][3];
