@@ -38,14 +38,12 @@ __global__ __launch_bounds__(block_threads<N>()) void k_rhs(RhsArgs<T> a, TO *ou
         // element_rhs, with the node's state kept for the fold
         NodeIn<T> in;
         node_gather<N, T, SHELL, GEO>(a, e, l, in);
+        const bool act = l < NP;
+        T Di[N + 1], Dj[N + 1], Dk[N + 1];
+        if (act) d_rows<N, T>(a.D, l, Di, Dj, Dk);  // in flight with the gather
         node_stage<N, T, SHELL, GEO>(a, e, l, in, s);
         __syncthreads();
-        const bool act = l < NP;
-        if (act) {
-            T Di[N + 1], Dj[N + 1], Dk[N + 1];
-            d_rows<N, T>(a.D, l, Di, Dj, Dk);
-            node_derive<N, T, SHELL, GEO>(a, l, in, Di, Dj, Dk, s, o);
-        }
+        if (act) node_derive<N, T, SHELL, GEO>(a, l, in, Di, Dj, Dk, s, o);
         __syncthreads();  // every lane has finished reading the tile
         TO *st = (TO *)&s[0][0];
         if (act) {
@@ -77,15 +75,213 @@ __global__ __launch_bounds__(block_threads<N>()) void k_rhs(RhsArgs<T> a, TO *ou
     }
 }
 
+// The element kernel of a shell stage with the recomputed metric, a lane per
+// (i, j) column: the two-pass tile of the box's k_elem_col2.  One node per lane
+// (k_rhs above) reads 15 tile values per field and node at N = 4 (27 contractions
+// of 5), forms every node's metric, gravity and reference loads for itself, and
+// waits for one gather at three waves per SIMD.  Here the tile holds p', u, v,
+// w, theta' (momentum and theta' rows), then rho u, rho v, rho w (mass row); the
+// zeta derivatives come from the lane's own column, which it reads once, the
+// column factors of the metric are loaded once per column, and the reference and
+// the layer factors, the same for all nodes of a level, once per level from one
+// address.  theta_bar varies along zeta only.
+template <int N, typename T> constexpr int shell_eb()
+{
+    constexpr int PP = (N + 1) * (N + 1), lanes = 256 / PP, lds = 81920 / (5 * PP * (N + 1) * (int)sizeof(T));
+    return lanes < lds ? lanes : lds;
+}
+template <int N, typename T> constexpr int shell_threads()
+{
+    return (shell_eb<N, T>() * (N + 1) * (N + 1) + 63) / 64 * 64;
+}
+// The column kernel from this many element-local nodes on: below, too few
+// workgroups with too long a chain each (one node per lane / columns, us per step,
+// at the element-local nodes before and after the line).  FP64: N = 1 12 k 36 / 38,
+// 29 k 43 / 39; 2: 41 k 33 / 40, 97 k 43 / 42; 3: 442 k 77 / 79, 786 k 116 / 107; 4:
+// 450 k 87 / 91, 864 k 139 / 128; 5: 187 k 60 / 67, 332 k 84 / 80; 6: 132 k 54 / 84,
+// 296 k 103 / 95; 7: 442 k 113 / 126, 786 k 170 / 160; 8: 2.6 M 652 / 709 (spills:
+// not taken).  Mixed: 3: 98 k 39 / 45, 230 k 51 / 49; 4: 450 k 72 / 80, 864 k 117 /
+// 114; 5: 778 k 116 / 117, 1.5 M 191 / 168; 6: 132 k 48 / 67, 296 k 84 / 77; 7: 1.8 M
+// 245 / 245; 8: 280 k 81 / 94, 630 k 141 / 134.
+template <int N, typename T> constexpr int64_t shell_col_from()
+{
+    constexpr int64_t f64[9] = {0, 20000, 90000, 600000, 700000, 300000, 250000, 700000, INT64_MAX};
+    constexpr int64_t f32[9] = {0, 20000, 90000, 200000, 800000, 800000, 250000, 2000000, 500000};
+    return sizeof(T) == 8 ? f64[N] : f32[N];
+}
+// Element kernel, one node per lane -> columns: 32x32x10 at N = 4 (61,440
+// elements) FP64 304 -> 234 us, mixed 221 -> 155; N = 2 83 -> 37; 20x20x8 at N = 5
+// 215 -> 137, mixed 133 -> 93; 16x16x8 at N = 6 273 -> 170, mixed 191 -> 101; 14x14x8
+// at N = 7 299 -> 205; mixed 12x12x8 at N = 8 255 -> 157.  Waves per SIMD: FP64 at
+// N = 4 three spill 128 bytes (282 against 234 us); mixed at N = 4 four with 16 bytes
+// of spill 155 against 170 us with three.
+template <int N, typename T> constexpr int shell_waves() { return sizeof(T) == 8 ? 2 : N <= 4 ? 4 : N == 5 ? 3 : 2; }
+template <int N, typename T>
+__global__ __launch_bounds__((shell_threads<N, T>()), (shell_waves<N, T>())) void k_shell_col(RhsArgs<T> a, int ne, T *out)
+{
+    constexpr int P = N + 1, PP = P * P, NP = PP * P, EB = shell_eb<N, T>(), BT = shell_threads<N, T>();
+    constexpr int PAD = sizeof(T) == 8 && N == 4 ? 8 : 0;  // spreads the lines over the LDS banks
+    __shared__ __align__(16) T s[EB][5 * NP + PAD];
+    const int e0 = (int)xcd_remap(blockIdx.x, gridDim.x) * EB;
+    const int t = threadIdx.x, q = t / PP, c = t % PP, i = c % P, j = c / P;
+    const bool act = q < EB && e0 + q < ne;
+    T *S = &s[act ? q : 0][0];
+    T Di[P], Dj[P];
+#pragma unroll
+    for (int m = 0; m < P; ++m) {
+        Di[m] = a.D[i * P + m];
+        Dj[m] = a.D[j * P + m];
+    }
+    // of the column: metric factors (xi, eta, zeta rows), J w, direction; of its
+    // nodes: rho, 1/rho, rho' (FP64) or rho'/rho
+    double F[9], jwc = 0.0, dn[3], rho[P];
+    T ir[P], bq[P], tb[P];
+    int ez = 0;
+    const double *lay = a.slay;
+    if (act) {
+        ez = (int)fdiv((uint32_t)(e0 + q), a.feh);
+        const int eh = e0 + q - ez * (int)a.feh.d;
+        lay = a.slay + 4 * ez * P;
+        const double *cp = a.scol + (int64_t)eh * (13 * PP) + c;
+#pragma unroll
+        for (int d = 0; d < 9; ++d) F[d] = cp[d * PP];
+        jwc = cp[9 * PP];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) dn[d] = cp[(10 + d) * PP];
+        const int64_t level = a.nh * ((int64_t)ez * N);
+        const double *qp = a.q + (level + a.shid[eh * PP + c]), *rf = a.ref + level;
+        double qv[P][5], rb[P], tbk[P], pb[P], x[P], pp[P];
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+#pragma unroll
+            for (int v = 0; v < 5; ++v) qv[k][v] = qp[v * a.nu + a.nh * k];
+            rb[k] = rf[a.nh * k];
+            tbk[k] = rf[a.nu + a.nh * k];
+            pb[k] = rf[2 * a.nu + a.nh * k];
+        }
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            x[k] = box_eos_x(qv[k][0], qv[k][4], rb[k], tbk[k]);
+            rho[k] = rb[k] + qv[k][0];
+            const double ird = 1.0 / rho[k];
+            ir[k] = (T)ird;
+            bq[k] = sizeof(T) == 8 ? (T)qv[k][0] : (T)(qv[k][0] * ird);
+            tb[k] = (T)(tbk[k] - tbk[0]);
+#pragma unroll
+            for (int v = 1; v < 5; ++v) S[v * NP + c + PP * k] = (T)qv[k][v];
+        }
+        eos_nodes<P>(P, x, pb, a.gamma, a.eos, pp);
+#pragma unroll
+        for (int k = 0; k < P; ++k) S[c + PP * k] = (T)pp[k];
+    }
+    auto metric = [&](int k, T *mx) {
+        const double r = lay[4 * k], z = lay[4 * k + 1];
+#pragma unroll
+        for (int d = 0; d < 9; ++d) mx[d] = (T)(F[d] * (d < 6 ? r : z));
+        mx[9] = (T)(jwc * lay[4 * k + 2]);
+    };
+    auto folds = [&](int k) { return a.fold && !((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N)); };
+    auto derive = [&](int f, int k, T *d) {
+        d[0] = dot<P>(Di, [&](int m) { return S[f * NP + m + P * (j + P * k)]; });
+        d[1] = dot<P>(Dj, [&](int m) { return S[f * NP + i + P * (m + P * k)]; });
+        d[2] = dot<P>(a.D + k * P, [&](int m) { return S[f * NP + c + PP * m]; });
+    };
+    const T cdt = (T)a.cdt;
+    T res[P][5];
+    __syncthreads();  // first tile complete
+    if (act) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            T mx[10], d[3], U[3], R[5];
+            metric(k, mx);
+            T qv[5];
+#pragma unroll
+            for (int v = 1; v < 5; ++v) qv[v] = S[v * NP + c + PP * k];
+#pragma unroll
+            for (int b = 0; b < 3; ++b) U[b] = qv[1] * mx[3 * b] + qv[2] * mx[3 * b + 1] + qv[3] * mx[3 * b + 2];
+#pragma unroll
+            for (int v = 1; v < 5; ++v) {
+                derive(v, k, d);
+                R[v] = -(U[0] * d[0] + U[1] * d[1] + U[2] * d[2]);
+            }
+            R[4] -= U[2] * dot<P>(a.D + k * P, [&](int m) { return tb[m]; });
+            derive(0, k, d);
+            const T bk = sizeof(T) == 8 ? bq[k] * ir[k] : bq[k];
+            const double ga = -lay[4 * k + 3];
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+                R[1 + b] += bk * (T)(ga * dn[b]) - (d[0] * mx[b] + d[1] * mx[3 + b] + d[2] * mx[6 + b]) * ir[k];
+            const bool fold = sizeof(T) == 8 && folds(k);
+#pragma unroll
+            for (int v = 1; v < 5; ++v) res[k][v] = mx[9] * (fold ? fma(cdt, R[v], qv[v]) : R[v]);
+            __builtin_amdgcn_sched_barrier(0);  // a node's lines at a time: registers
+        }
+    }
+    // the mass fluxes, formed from the first tile
+    T fl[P][3];
+    if (act) {
+#pragma unroll
+        for (int k = 0; k < P; ++k)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) fl[k][b] = (T)(rho[k] * (double)S[(1 + b) * NP + c + PP * k]);
+    }
+    __syncthreads();  // first tile read
+    if (act) {
+#pragma unroll
+        for (int k = 0; k < P; ++k)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) S[b * NP + c + PP * k] = fl[k][b];
+    }
+    __syncthreads();  // second tile complete
+    if (act) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            T mx[10], dv = 0;
+            metric(k, mx);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                T d[3];
+                d[0] = dot<P>(Di, [&](int m) { return S[b * NP + m + P * (j + P * k)]; });
+                d[1] = dot<P>(Dj, [&](int m) { return S[b * NP + i + P * (m + P * k)]; });
+                d[2] = dot<P>(a.D + k * P, [&](int m) { return fl[m][b]; });
+                dv += d[0] * mx[b] + d[1] * mx[3 + b] + d[2] * mx[6 + b];
+            }
+            const bool fold = sizeof(T) == 8 && folds(k);
+            res[k][0] = mx[9] * (fold ? fma(cdt, -dv, bq[k]) : -dv);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();  // second tile read
+    T *st = &s[0][0];
+    if (act) {
+#pragma unroll
+        for (int k = 0; k < P; ++k)
+#pragma unroll
+            for (int v = 0; v < 5; ++v) st[(q * NP + c + PP * k) * 5 + v] = res[k][v];
+    }
+    __syncthreads();
+    // the workgroup's elements are consecutive: one contiguous run
+    const int nel = ne - e0 < EB ? ne - e0 : EB;
+    store_run<T>(out + (int64_t)e0 * (NP * 5), st, nel * NP * 5, t, BT);
+}
+
 template <int N, typename T, typename TO>
 void launch_n(Mesh &m, const RhsArgs<T> &a, TO *out, bool node_major, hipStream_t s)
 {
     dim3 grid((unsigned)m.ne), block(block_threads<N>());
     if constexpr (sizeof(TO) == sizeof(T)) {
         if (node_major && m.d.kind == NUMA_MESH_SHELL) {
-            if (m.metric_mode == NUMA_METRIC_RECOMPUTE)
-                hipLaunchKernelGGL((k_rhs<N, T, TO, true, kMetricShell, true>), grid, block, 0, s, a, out);
-            else
+            if (m.metric_mode == NUMA_METRIC_RECOMPUTE) {
+                if (m.nl < shell_col_from<N, T>()) {
+                    hipLaunchKernelGGL((k_rhs<N, T, TO, true, kMetricShell, true>), grid, block, 0, s, a, out);
+                    return;
+                }
+                if constexpr (shell_col_from<N, T>() < INT64_MAX) {
+                    constexpr int EB = shell_eb<N, T>();
+                    hipLaunchKernelGGL((k_shell_col<N, T>), dim3((unsigned)((m.ne + EB - 1) / EB)),
+                                       dim3(shell_threads<N, T>()), 0, s, a, (int)m.ne, out);
+                }
+            } else
                 hipLaunchKernelGGL((k_rhs<N, T, TO, true, kMetricStored, true>), grid, block, 0, s, a, out);
             return;
         }
