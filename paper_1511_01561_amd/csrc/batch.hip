@@ -171,11 +171,11 @@ __global__ __launch_bounds__(block_threads<N>(), N == 8 && sizeof(T) == 4 ? 6 : 
     // element_rhs, with the node's state kept for the fold
     NodeIn<T> in;
     node_gather<N, T, false, GEO>(a, e, l, in);
-    T Di[N + 1], Dj[N + 1], Dk[N + 1];
-    if (act) d_rows<N, T>(a.D, l, Di, Dj, Dk);  // in flight with the gather
     node_stage<N, T, false, GEO>(a, e, l, in, s);
     __syncthreads();
     if (act) {
+        T Di[N + 1], Dj[N + 1], Dk[N + 1];
+        d_rows<N, T>(a.D, l, Di, Dj, Dk);
         const int k = l / ((N + 1) * (N + 1));
         const bool wall = it.walls && ((in.ez == 0 && k == 0) || (in.ez == it.nz - 1 && k == N));
         const bool fold = sizeof(T) == 8 && B.fold && !wall;

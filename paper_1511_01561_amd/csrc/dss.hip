@@ -2,11 +2,10 @@
 // SSP-RK3 stage update (the pointwise part of each stage in Code example 1:
 // "DSS and multiply with inverse mass matrix", "update q").
 //
-// The summation is a gather over the inverse of the element -> unique map:
-// each unique node sums its element-local copies in ascending order.  No
-// atomics, no colouring and no barriers are needed, and the result does not
-// depend on scheduling (the paper avoids atomics by re-ordering elements and
-// adding barriers; a gather removes the race altogether).
+// The summation is a gather: each unique node sums its element-local copies in
+// ascending order.  No atomics, no colouring and no barriers are needed, and the
+// result does not depend on scheduling (the paper avoids atomics by re-ordering
+// elements and adding barriers; a gather removes the race altogether).
 #include "kernels.h"
 
 namespace numa {
@@ -14,25 +13,109 @@ namespace {
 
 using namespace dev;
 
-__global__ void k_dss(PointArgs p, int nvar, const double *cin, double *out, int flags)
+// Where the copies of a unique node are: the box's follow from its lattice
+// position (I = gi + ni (gj + nj gk): two elements per direction on an element
+// face, wrapped where periodic), the shell's are its horizontal copies in the
+// bottom layer (hoff/hidx) in each radial layer that holds its level.  Nothing
+// but the copies themselves is read (the shell: its short horizontal list), where
+// the inverse map costs 4 bytes per copy and puts a load in front of every copy
+// (17x13x7, N = 5: 14.5 -> DSSUS us).
+struct DssGeo {
+    FastDiv fi, fj;            // box: division by ni and nj; shell: fi by n_horiz
+    int nx, ny, nz, walls;     // elements; shell: nz layers
+    const int32_t *hoff, *hidx;
+    int layer;                 // shell: element-local nodes of one layer
+};
+
+// the copies of node I (e (N+1)^3 + l): eight slots, the used ones ascending, the
+// others -1
+template <int N, bool SHELL>
+__device__ __forceinline__ void node_copies(const DssGeo &g, uint32_t I, int *cc)
 {
-    int64_t I = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    constexpr int P = N + 1, PP = P * P, NP = PP * P;
+    // the two elements (and local indices) of lattice index c of n elements, in
+    // ascending element order, the second -1 where there is none
+    auto pair = [](int c, int n, bool wrap, int *e, int *l) {
+        e[0] = c / N;
+        l[0] = c - e[0] * N;
+        e[1] = -1;
+        l[1] = 0;
+        if (e[0] == n) {  // the top level
+            e[0] = n - 1;
+            l[0] = N;
+        } else if (l[0] == 0 && e[0] > 0) {
+            e[1] = e[0];
+            e[0] -= 1;
+            l[0] = N;
+        } else if (l[0] == 0 && wrap) {
+            e[1] = n - 1;
+            l[1] = N;
+        }
+    };
+    int ez[2], lz[2];
+    const uint32_t t = fdiv(I, g.fi);
+    const int gi = (int)(I - t * g.fi.d);
+    if constexpr (SHELL) {
+        pair((int)t, g.nz, false, ez, lz);
+        const int hb = g.hoff[gi], hn = g.hoff[gi + 1] - hb;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const int c = h < hn ? g.hidx[hb + h] : -1;
+#pragma unroll
+            for (int z = 0; z < 2; ++z) cc[4 * z + h] = h < hn && ez[z] >= 0 ? ez[z] * g.layer + PP * lz[z] + c : -1;
+        }
+    } else {
+        const uint32_t gk = fdiv(t, g.fj);
+        int ex[2], lx[2], ey[2], ly[2];
+        pair((int)gk, g.nz, !g.walls, ez, lz);
+        pair((int)(t - gk * g.fj.d), g.ny, true, ey, ly);
+        pair(gi, g.nx, true, ex, lx);
+#pragma unroll
+        for (int z = 0; z < 2; ++z)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                for (int x = 0; x < 2; ++x)
+                    cc[4 * z + 2 * y + x] = ez[z] >= 0 && ey[y] >= 0 && ex[x] >= 0
+                                                ? (ex[x] + g.nx * (ey[y] + g.ny * ez[z])) * NP + lx[x] +
+                                                      P * (ly[y] + P * lz[z])
+                                                : -1;
+    }
+}
+
+template <int N, bool SHELL>
+__global__ __launch_bounds__(256) void k_dss(PointArgs p, DssGeo g, int nvar, const double *cin, double *out, int flags)
+{
+    const int64_t I = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (I >= p.nu) return;
-    const int32_t b = p.off[I], en = p.off[I + 1];
+    int cc[8];
+    node_copies<N, SHELL>(g, (uint32_t)I, cc);
     double r[5] = {0, 0, 0, 0, 0};
     const bool mass = flags & NUMA_DSS_MASS;
     const double mi = mass ? p.Minv[I] : 1.0;
     for (int v0 = 0; v0 < nvar; v0 += 5) {
-        int nv = nvar - v0 < 5 ? nvar - v0 : 5;
-        for (int v = 0; v < nv; ++v) r[v] = 0.0;
-        for (int32_t c = b; c < en; ++c) {
-            int64_t cc = p.idx[c];
-            for (int v = 0; v < nv; ++v) r[v] += cin[(v0 + v) * p.nl + cc];
-        }
+        const int nv = nvar - v0 < 5 ? nvar - v0 : 5;
+        // absent copies are not loaded; the present ones are added in ascending order
+        double c[8][5];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int v = 0; v < 5; ++v)
+                c[k][v] = cc[k] >= 0 && v < nv ? cin[(v0 + v) * p.nl + cc[k]] : 0.0;
+#pragma unroll
+        for (int v = 0; v < 5; ++v) r[v] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (cc[k] >= 0)
+#pragma unroll
+                for (int v = 0; v < 5; ++v) r[v] += c[k][v];
         if (mass)
-            for (int v = 0; v < nv; ++v) r[v] *= mi;
+#pragma unroll
+            for (int v = 0; v < 5; ++v) r[v] *= mi;
         if ((flags & NUMA_DSS_NOFLUX) && nvar == 5) noflux(p, I, r[1], r[2], r[3]);
-        for (int v = 0; v < nv; ++v) out[(v0 + v) * p.nu + I] = r[v];
+#pragma unroll
+        for (int v = 0; v < 5; ++v)
+            if (v < nv) out[(v0 + v) * p.nu + I] = r[v];
     }
 }
 
@@ -166,8 +249,36 @@ void launch_shell_finish_t(Mesh &m, const T *ev, const StageCoef &c, const doubl
 
 int32_t launch_dss(Mesh &m, int32_t nvar, const double *cin, double *out, int32_t flags, hipStream_t s)
 {
-    PointArgs p = point_args(m);
-    hipLaunchKernelGGL(k_dss, dim3(nblocks(m.nu, 256)), dim3(256), 0, s, p, nvar, cin, out, flags);
+    const bool shell = m.d.kind == NUMA_MESH_SHELL;
+    const PointArgs p = point_args(m);
+    DssGeo g{};
+    g.fi = fast_div((uint32_t)(shell ? m.nh : m.ni));
+    g.fj = fast_div((uint32_t)(shell ? 1 : m.nj));
+    g.nx = m.d.ne[0];
+    g.ny = m.d.ne[1];
+    g.nz = m.d.ne[2];
+    g.walls = m.walls ? 1 : 0;
+    g.hoff = m.dv.hoff;
+    g.hidx = m.dv.hidx;
+    g.layer = shell ? 6 * m.d.ne[0] * m.d.ne[0] * m.np : 0;
+    const dim3 grid(nblocks(m.nu, 256)), block(256);
+    auto launch = [&](auto order) {
+        constexpr int N = decltype(order)::value;
+        if (shell)
+            hipLaunchKernelGGL((k_dss<N, true>), grid, block, 0, s, p, g, nvar, cin, out, flags);
+        else
+            hipLaunchKernelGGL((k_dss<N, false>), grid, block, 0, s, p, g, nvar, cin, out, flags);
+    };
+    switch (m.N) {
+    case 1: launch(std::integral_constant<int, 1>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    case 3: launch(std::integral_constant<int, 3>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 5: launch(std::integral_constant<int, 5>{}); break;
+    case 6: launch(std::integral_constant<int, 6>{}); break;
+    case 7: launch(std::integral_constant<int, 7>{}); break;
+    default: launch(std::integral_constant<int, 8>{}); break;
+    }
     NUMA_HIP(hipGetLastError());
     return NUMA_OK;
 }

@@ -309,8 +309,7 @@ __device__ __forceinline__ void node_stage(const RhsArgs<T> &a, int64_t e, int l
     constexpr int NP = (N + 1) * (N + 1) * (N + 1);
     if (l >= NP) return;
     const double rho = in.rb + in.rp, x = box_eos_x(in.rp, in.tp, in.rb, in.tb);
-    double pp;
-    eos_nodes<1>(1, &x, &in.pb, a.gamma, a.eos, &pp);
+    const double pp = in.pb * eos_rel(x, a.gamma, a.eos);
     s[0][l] = (T)(rho * in.u);
     s[1][l] = (T)(rho * in.v);
     s[2][l] = (T)(rho * in.w);
@@ -429,7 +428,18 @@ __device__ __forceinline__ void node_derive(const RhsArgs<T> &a, int l, const No
     } else {
         T dd[9][3];
 #pragma unroll
-        for (int f = 0; f < 9; ++f) derive(f, dd[f], true, true);
+        for (int f = 0; f < 9; ++f) {
+            T da = 0, db = 0, dc = 0;
+#pragma unroll
+            for (int m = 0; m < P; ++m) {
+                da += Di[m] * s[f][m + P * (j + P * k)];
+                db += Dj[m] * s[f][i + P * (m + P * k)];
+                dc += Dk[m] * s[f][i + P * (j + P * m)];
+            }
+            dd[f][0] = da;
+            dd[f][1] = db;
+            dd[f][2] = dc;
+        }
         T gv[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) gv[d] = GEO == kMetricShell ? in.gv[d] : (T)a.grav[d * a.nu + in.I];

@@ -38,12 +38,14 @@ __global__ __launch_bounds__(block_threads<N>()) void k_rhs(RhsArgs<T> a, TO *ou
         // element_rhs, with the node's state kept for the fold
         NodeIn<T> in;
         node_gather<N, T, SHELL, GEO>(a, e, l, in);
-        const bool act = l < NP;
-        T Di[N + 1], Dj[N + 1], Dk[N + 1];
-        if (act) d_rows<N, T>(a.D, l, Di, Dj, Dk);  // in flight with the gather
         node_stage<N, T, SHELL, GEO>(a, e, l, in, s);
         __syncthreads();
-        if (act) node_derive<N, T, SHELL, GEO>(a, l, in, Di, Dj, Dk, s, o);
+        const bool act = l < NP;
+        if (act) {
+            T Di[N + 1], Dj[N + 1], Dk[N + 1];
+            d_rows<N, T>(a.D, l, Di, Dj, Dk);
+            node_derive<N, T, SHELL, GEO>(a, l, in, Di, Dj, Dk, s, o);
+        }
         __syncthreads();  // every lane has finished reading the tile
         TO *st = (TO *)&s[0][0];
         if (act) {
