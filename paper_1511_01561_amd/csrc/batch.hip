@@ -176,10 +176,15 @@ __global__ __launch_bounds__(block_threads<N>(), N == 8 && sizeof(T) == 4 ? 6 : 
     if (act) {
         T Di[N + 1], Dj[N + 1], Dk[N + 1];
         d_rows<N, T>(a.D, l, Di, Dj, Dk);
+        node_derive<N, T, false, GEO>(a, l, in, Di, Dj, Dk, s, o);
+        // J w R, or J w (q_s + cdt R) away from the walls when folding
         const int k = l / ((N + 1) * (N + 1));
         const bool wall = it.walls && ((in.ez == 0 && k == 0) || (in.ez == it.nz - 1 && k == N));
-        const bool fold = sizeof(T) == 8 && B.fold && !wall;
-        node_derive<N, T, false, GEO>(a, l, in, Di, Dj, Dk, s, o, {fold ? (T)it.cdt : T(1), fold});
+        if (sizeof(T) == 8 && B.fold && !wall) {
+            const double qv[5] = {in.rp, in.u, in.v, in.w, in.tp};
+#pragma unroll
+            for (int v = 0; v < 5; ++v) o.R[v] = fma((T)it.cdt, o.R[v], (T)qv[v]);
+        }
     }
     __syncthreads();  // every lane has finished reading the tile
     T *st = &s[0][0];
@@ -523,25 +528,22 @@ __global__ __launch_bounds__((col_threads<N, T>()), (col_blocks<N, T, MODE>())) 
             const T bk = F64 ? buoy[k] * irho[k] : buoy[k];
             // J w R, or J w (q_s + cdt R) away from the walls when folding
             const bool wall = it.walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
-            const bool fold = F64 && B.fold && !wall;
-            T U[3], pr[3];
+            T R[5], U[3], adv[4];
             box_velocity<T>(mx, uu, vv, ww, U);
-            box_pressure<T>(mx, dd[7], irho[k], bk, (T)(-a.g0), pr);
-            const T qv[4] = {uu, vv, ww, s[q][6][l]}, dzm[3] = {dd[0][2], dd[1][2], dd[2][2]};
-            // a branch, not a select: it keeps a node's values apart from the next one's
-            auto terms = [&](const FoldTerms<T> ft) {
 #pragma unroll
-                for (int f = 0; f < 4; ++f) {
-                    T r = fm(-ft.s, box_advect<T>(U, dd[3 + f]), ft.base(qv[f]));
-                    if (f < 3) r = fm(ft.s, pr[f], r);
-                    res[k][1 + f] = mx[9] * r;
-                }
-                res[k][0] = mx[9] * fm(ft.s, box_mass<T>(mx, dd[0][0], dd[1][1], dzm), ft.base(buoy[k]));
-            };
-            if (fold)
-                terms({(T)it.cdt, true});
-            else
-                terms({T(1), false});
+            for (int f = 0; f < 4; ++f) adv[f] = box_advect<T>(U, dd[3 + f]);
+            box_momentum<T>(mx, adv, dd[7], irho[k], bk, (T)(-a.g0), R + 1);
+            R[4] = -adv[3];
+            const T dzm[3] = {dd[0][2], dd[1][2], dd[2][2]};
+            R[0] = box_mass<T>(mx, dd[0][0], dd[1][1], dzm);
+            if (F64 && B.fold && !wall) {
+                const T qv[5] = {buoy[k], uu, vv, ww, s[q][6][l]};
+#pragma unroll
+                for (int v = 0; v < 5; ++v) res[k][v] = mx[9] * fma((T)it.cdt, R[v], qv[v]);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 5; ++v) res[k][v] = mx[9] * R[v];
+            }
         }
     }
     if constexpr (MODE == 1) {
@@ -700,16 +702,19 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
             if constexpr (F64) ir[k] = (T)(1.0 / rho[k]);
             const T bk = F64 ? bq[k] * ir[k] : bq[k];
             const bool wall = walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
-            const FoldTerms<T> ft{fold && !wall ? (T)cdt : T(1), fold && !wall};
-            T U[3], pr[3];
+            T R[4], U[3], adv[4];
             box_velocity<T>(mx, uu, vv, ww, U);
-            box_pressure<T>(mx, dd[0], ir[k], bk, (T)gz, pr);
-            const T qv[4] = {uu, vv, ww, tt};
 #pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                T r = fm(-ft.s, box_advect<T>(U, dd[1 + f]), ft.base(qv[f]));
-                if (f < 3) r = fm(ft.s, pr[f], r);
-                res[k][1 + f] = mx[9] * r;
+            for (int f = 0; f < 4; ++f) adv[f] = box_advect<T>(U, dd[1 + f]);
+            box_momentum<T>(mx, adv, dd[0], ir[k], bk, (T)gz, R);
+            R[3] = -adv[3];
+            if (fold && !wall) {
+                const T qv[4] = {uu, vv, ww, tt};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) res[k][v + 1] = mx[9] * fma((T)cdt, R[v], qv[v]);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) res[k][v + 1] = mx[9] * R[v];
             }
             __builtin_amdgcn_sched_barrier(0);  // a node's rows at a time: registers
         }
@@ -747,8 +752,8 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
 #pragma unroll
             for (int f = 0; f < 3; ++f) dz[f] = dot<P>(a.D + k * P, [&](int m) { return fl[m][f]; });
             const bool wall = walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
-            const FoldTerms<T> ft{fold && !wall ? (T)cdt : T(1), fold && !wall};
-            res[k][0] = mx[9] * fm(ft.s, box_mass<T>(mx, da, db, dz), ft.base(bq[k]));
+            const T R0 = box_mass<T>(mx, da, db, dz);
+            res[k][0] = (fold && !wall) ? mx[9] * fma((T)cdt, R0, bq[k]) : mx[9] * R0;
         }
     }
     // the run-interior nodes' M^-1 and q^n (issued here, where the tiles'
@@ -836,6 +841,13 @@ __global__ __launch_bounds__((split_threads<N>()), 2) void k_elem_rows(Batch B)
         }
     };
     double rho[P], bq[P], pp[P], uv[2][P], res[P][5];
+    int base = 0;
+    const int layer = a.ni * a.nj;
+    auto at = [&](int k) {  // unique id of the column's node k
+        int gk = ez * N + k;
+        if (gk == a.nk) gk = 0;
+        return base + layer * gk;
+    };
     if (act) {
         const BoxElem be = box_elem((uint32_t)(e0 + q), a.fx, a.fy);
         ez = be.ez;
@@ -849,7 +861,7 @@ __global__ __launch_bounds__((split_threads<N>()), 2) void k_elem_rows(Batch B)
         int gi = be.ex * N + i, gj = be.ey * N + j;
         if (gi == a.ni) gi = 0;
         if (gj == a.nj) gj = 0;
-        const int base = gi + a.ni * gj, layer = a.ni * a.nj;
+        base = gi + a.ni * gj;
         gather_column<P, P>(a, it.theta0, base, layer, be.ez * N,
                             [&](int k, const double *qv, double rb, double p) {
                                 rho[k] = rb + qv[0];
@@ -864,10 +876,10 @@ __global__ __launch_bounds__((split_threads<N>()), 2) void k_elem_rows(Batch B)
                             });
         if constexpr (STORED) fetch(0);
     }
-    // where node k folds q_s in: FoldTerms
-    auto terms = [&](int k) -> FoldTerms<T> {
+    // J w (q_s + cdt R) where node k folds q_s in, else J w R
+    auto value = [&](int k, double jw, double R, double qs) {
         const bool wall = it.walls && ((ez == 0 && k == 0) || (ez == a.nz - 1 && k == N));
-        return {fold && !wall ? cdt : 1.0, fold && !wall};
+        return jw * (fold && !wall ? fma(cdt, R, qs) : R);
     };
     double dx[P], de[P];
     auto line = [&](auto at, int f, double *d) {
@@ -908,8 +920,7 @@ __global__ __launch_bounds__((split_threads<N>()), 2) void k_elem_rows(Batch B)
                 double mx[10];
                 metric(k, mx);
                 const double dk[3] = {dz[0][k], dz[1][k], dz[2][k]};
-                const FoldTerms<T> ft = terms(k);
-                res[k][0] = mx[9] * fm(ft.s, box_mass<T>(mx, node(SU, k), node(SV, k), dk), ft.base(bq[k]));
+                res[k][0] = value(k, mx[9], box_mass<T>(mx, node(SU, k), node(SV, k), dk), bq[k]);
                 box_velocity<T>(mx, uv[0][k], uv[1][k], node(SW, k), U[k]);
             }
     }
@@ -922,10 +933,16 @@ __global__ __launch_bounds__((split_threads<N>()), 2) void k_elem_rows(Batch B)
         }
     // theta', w, v, u, then p' from theta''s slot, free by then; u and v are
     // stored two barriers before their lines are read
+    double qr[P][4];
 #pragma unroll
     for (int step = 0; step < 5; ++step) {
         const int f = step == 4 ? ST : ST - step;
         double cf[P], d2[P];
+        if (step == 4 && act && fold)  // the state again (from the caches), for the fold
+#pragma unroll
+            for (int k = 0; k < P; ++k)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) qr[k][v] = a.q[at(k) + (1 + v) * a.nu];
         if (act) {
             line(xi, f, dx);
             line(eta, f, de);
@@ -950,18 +967,16 @@ __global__ __launch_bounds__((split_threads<N>()), 2) void k_elem_rows(Batch B)
 #pragma unroll
             for (int k = 0; k < P; ++k) {
                 const double d[3] = {node(f, k), node(SE, k), d2[k]};
-                const FoldTerms<T> ft = terms(k);
                 if (step < 4) {
-                    const double r = fm(-ft.s, box_advect<T>(U[k], d), ft.base(cf[k]));
-                    res[k][1 + f] = r;
+                    res[k][1 + f] = box_advect<T>(U[k], d);
                 } else {
-                    double mx[10], pr[3];
+                    double mx[10], R[4];
                     metric(k, mx);
                     const double ir = 1.0 / rho[k];
-                    box_pressure<T>(mx, d, ir, bq[k] * ir, gz, pr);
+                    box_momentum<T>(mx, res[k] + 1, d, ir, bq[k] * ir, gz, R);
+                    R[3] = -res[k][4];
 #pragma unroll
-                    for (int v = 0; v < 3; ++v) res[k][1 + v] = mx[9] * fm(ft.s, pr[v], res[k][1 + v]);
-                    res[k][4] = mx[9] * res[k][4];
+                    for (int v = 0; v < 4; ++v) res[k][1 + v] = value(k, mx[9], R[v], qr[k][v]);
                 }
             }
     }
@@ -1308,22 +1323,23 @@ __global__ __launch_bounds__((col_threads<N, T>())) void k_elem_stream(Batch B)
                 const T dc = dot<P>(D + k * P, [&](int m) { return cf[m]; });
                 if (f != 1 && f != 2) da = dot<P>(Di, [&](int m) { return s[q][f][m + P * (j + P * k)]; });
                 if (f != 0 && f != 2) db = dot<P>(Dj, [&](int m) { return s[q][f][i + P * (m + P * k)]; });
-                // the operations of box_mass, box_advect and box_pressure, a field at a time
+                // the operations of box_mass, box_advect and box_momentum, a field at a time
                 if (f == 0) R[k][0] = fm(dc, mx6, da * mx0);              // d(rho u)/dx
                 if (f == 1) R[k][0] = R[k][0] + fm(dc, mx7, db * mx4);    // + d(rho v)/dy
                 if (f == 2) R[k][0] = -fm(dc, mx8, R[k][0]);              // + d(rho w)/dz
                 const T dd[3] = {da, db, dc};
-                if (f >= 3 && f <= 6) R[k][f - 2] = -box_advect<T>(Uc[k], dd);
+                if (f >= 3 && f <= 6) R[k][f - 2] = box_advect<T>(Uc[k], dd);
                 if (f == 7) {
-                    T mx[10], pr[3];
+                    T mx[10], Rm[3];
                     mx[0] = mx0;
                     mx[4] = mx4;
                     mx[6] = mx6;
                     mx[7] = mx7;
                     mx[8] = mx8;
-                    box_pressure<T>(mx, dd, irho[k], buoy[k], (T)(-a.g0), pr);
+                    box_momentum<T>(mx, R[k] + 1, dd, irho[k], buoy[k], (T)(-a.g0), Rm);
 #pragma unroll
-                    for (int v = 0; v < 3; ++v) R[k][1 + v] = pr[v] + R[k][1 + v];
+                    for (int v = 0; v < 3; ++v) R[k][1 + v] = Rm[v];
+                    R[k][4] = -R[k][4];
                 }
             }
         }

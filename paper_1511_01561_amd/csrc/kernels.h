@@ -108,26 +108,17 @@ __device__ __forceinline__ T box_advect(const T *U, const T *d)
     return fm(U[2], d[2], fm(U[1], d[1], U[0] * d[0]));
 }
 
-// pressure gradient and buoyancy of the momentum rows from the reference
-// derivatives of p' (dp), 1/rho and bk = rho'/rho
+// the momentum rows of R from the advection of u, v, w (adv), the reference
+// derivatives of p' (dp), 1/rho and bk = rho'/rho: advection, pressure
+// gradient, buoyancy
 template <typename T>
-__device__ __forceinline__ void box_pressure(const T *mx, const T *dp, T ir, T bk, T gz, T *R)
+__device__ __forceinline__ void box_momentum(const T *mx, const T *adv, const T *dp, T ir, T bk, T gz, T *R)
 {
 #pragma clang fp contract(off)
-    R[0] = -(fm(dp[2], mx[6], dp[0] * mx[0]) * ir);
-    R[1] = -(fm(dp[2], mx[7], dp[1] * mx[4]) * ir);
-    R[2] = fm(bk, gz, -(dp[2] * mx[8] * ir));
+    R[0] = -fm(fm(dp[2], mx[6], dp[0] * mx[0]), ir, adv[0]);
+    R[1] = -fm(fm(dp[2], mx[7], dp[1] * mx[4]), ir, adv[1]);
+    R[2] = fm(bk, gz, -fm(dp[2] * mx[8], ir, adv[2]));
 }
-
-// The value a node contributes, before J w: b + s R with (s, b) = (cdt, q_s) where
-// the stage state is folded in, else (1, 0); R a sum of terms added one after
-// another (the advection's first): fm(s, term, b)
-template <typename T>
-struct FoldTerms {
-    T s;
-    bool on;
-    __device__ __forceinline__ T base(T q) const { return on ? q : T(0); }
-};
 
 // the mass row: da = d(rho u)/dxi, db = d(rho v)/deta, dz = d(rho u, rho v, rho w)/dzeta
 template <typename T>
@@ -206,7 +197,7 @@ __device__ __forceinline__ int32_t box_unique(const RhsArgs<T> &a, const BoxElem
 template <int N>
 constexpr int block_threads() { return (((N + 1) * (N + 1) * (N + 1) + 63) / 64) * 64; }
 
-// Per-node result of the element RHS (on the box b + s R, FoldTerms).
+// Per-node result of the element RHS.
 template <typename T>
 struct NodeOut {
     T R[5];  // R_rho', R_u, R_v, R_w, R_theta'
@@ -385,7 +376,7 @@ __device__ __forceinline__ void shell_combine(const T (*dd)[3], const T *mx, dou
 template <int N, typename T, bool SHELL, int GEO>
 __device__ __forceinline__ void node_derive(const RhsArgs<T> &a, int l, const NodeIn<T> &in, const T *Di,
                                             const T *Dj, const T *Dk, T (*s)[(N + 1) * (N + 1) * (N + 1)],
-                                            NodeOut<T> &o, FoldTerms<T> fold = {T(1), false})
+                                            NodeOut<T> &o)
 {
     constexpr int P = N + 1, PP = P * P;
     const int i = l % P, j = (l / P) % P, k = l / PP;
@@ -407,23 +398,21 @@ __device__ __forceinline__ void node_derive(const RhsArgs<T> &a, int l, const No
             for (int c = 6; c < 10; ++c) mx[c] = in.mx[c];
         }
         const double ird = 1.0 / (in.rb + in.rp);
-        T U[3], d[3], pr[3], fu[3], fv[3], fw[3];
+        T U[3], adv[4], d[3], fu[3], fv[3], fw[3];
         box_velocity<T>(mx, (T)in.u, (T)in.v, (T)in.w, U);
-        const T q[4] = {(T)in.u, (T)in.v, (T)in.w, (T)in.tp};
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
             derive(3 + f, d, true, true);
-            o.R[1 + f] = fm(-fold.s, box_advect<T>(U, d), fold.base(q[f]));
+            adv[f] = box_advect<T>(U, d);
         }
         derive(7, d, true, true);
-        box_pressure<T>(mx, d, (T)ird, (T)(in.rp * ird), (T)(-a.g0), pr);
-#pragma unroll
-        for (int f = 0; f < 3; ++f) o.R[1 + f] = fm(fold.s, pr[f], o.R[1 + f]);
+        box_momentum<T>(mx, adv, d, (T)ird, (T)(in.rp * ird), (T)(-a.g0), o.R + 1);
+        o.R[4] = -adv[3];
         derive(0, fu, true, false);
         derive(1, fv, false, true);
         derive(2, fw, false, false);
         const T dz[3] = {fu[2], fv[2], fw[2]};
-        o.R[0] = fm(fold.s, box_mass<T>(mx, fu[0], fv[1], dz), fold.base((T)in.rp));
+        o.R[0] = box_mass<T>(mx, fu[0], fv[1], dz);
         o.Jw = mx[9];
     } else {
         T dd[9][3];
