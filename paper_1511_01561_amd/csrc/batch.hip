@@ -177,20 +177,21 @@ __global__ __launch_bounds__(block_threads<N>(), N == 8 && sizeof(T) == 4 ? 6 : 
         T Di[N + 1], Dj[N + 1], Dk[N + 1];
         d_rows<N, T>(a.D, l, Di, Dj, Dk);
         node_derive<N, T, false, GEO>(a, l, in, Di, Dj, Dk, s, o);
-        // J w R, or J w (q_s + cdt R) away from the walls when folding
-        const int k = l / ((N + 1) * (N + 1));
-        const bool wall = it.walls && ((in.ez == 0 && k == 0) || (in.ez == it.nz - 1 && k == N));
-        if (sizeof(T) == 8 && B.fold && !wall) {
-            const double qv[5] = {in.rp, in.u, in.v, in.w, in.tp};
-#pragma unroll
-            for (int v = 0; v < 5; ++v) o.R[v] = fma((T)it.cdt, o.R[v], (T)qv[v]);
-        }
     }
     __syncthreads();  // every lane has finished reading the tile
     T *st = &s[0][0];
-    if (act)
+    if (act) {
+        const int k = l / ((N + 1) * (N + 1));
+        const bool wall = it.walls && ((in.ez == 0 && k == 0) || (in.ez == it.nz - 1 && k == N));
+        if (sizeof(T) == 8 && B.fold && !wall) {  // J w (q_s + cdt R), as in k_elem_col
+            const double qv[5] = {in.rp, in.u, in.v, in.w, in.tp};
 #pragma unroll
-        for (int v = 0; v < 5; ++v) st[l * 5 + v] = o.Jw * o.R[v];
+            for (int v = 0; v < 5; ++v) st[l * 5 + v] = o.Jw * fma((T)it.cdt, o.R[v], (T)qv[v]);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 5; ++v) st[l * 5 + v] = o.Jw * o.R[v];
+        }
+    }
     __syncthreads();
     store_contributions<N, T>(it, e, l, st);
 }
