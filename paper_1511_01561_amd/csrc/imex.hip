@@ -109,37 +109,61 @@ __device__ __forceinline__ void level_factors(const ImexArgs &a, int g, double &
     }
 }
 
-// (G)_{g m} on a line of nk = nz N + 1 levels
+// G on a line of nk = nz N + 1 levels: (G)_{g m} = g_num / g_den.  Level g
+// takes element g / N and, on an element boundary, the one below.  D and w in
+// LDS (a lane's own indices: from the kernel arguments each would be a global
+// load).
+template <int N, typename F>
+__device__ __forceinline__ void g_elements(int nk, int g, F f)
+{
+    const int eg = g / N, kg = g - eg * N;
+    if (g != nk - 1) f(eg, kg);  // the top wall node: element below only
+    if (kg == 0 && eg != 0) f(eg - 1, N);
+}
+
 template <int N>
-__device__ double g_entry(const ImexArgs &a, const LineGeo &lg, int g, int m)
+__device__ __forceinline__ double g_den(const ImexArgs &a, const LineGeo &lg, const double *w, int g)
+{
+    double den = 0.0;
+    g_elements<N>(a.nk, g, [&](int e, int k) { den += h_of<N>(a, lg, e, k) * w[k]; });
+    return den;
+}
+
+template <int N>
+__device__ __forceinline__ double g_num(const double *D, const double *w, int nk, int g, int m)
 {
     constexpr int P = N + 1;
-    double num = 0.0, den = 0.0;
-    const int eg = g / N, kg = g - eg * N;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        // element eg (local kg) and, on an element boundary, eg - 1 (local N)
-        const int e = s == 0 ? eg : eg - 1, k = s == 0 ? kg : N;
-        if (s == 0 && g == a.nk - 1) continue;  // top wall node: element below only
-        if (s == 1 && (kg != 0 || eg == 0)) continue;
-        den += h_of<N>(a, lg, e, k) * a.w[k];
+    double num = 0.0;
+    g_elements<N>(nk, g, [&](int e, int k) {
         const int km = m - e * N;
-        if (km >= 0 && km <= N) num += a.w[k] * a.D[k * P + km];
-    }
-    return num / den;
+        if (km >= 0 && km <= N) num += w[k] * D[k * P + km];
+    });
+    return num;
 }
 
 // The factors of A for every line: one 64-lane workgroup per line builds the
-// band of G and of A in LDS, factors it and writes the band out.
+// band of G and of A in LDS, factors it and writes the band out.  Bound by the
+// chain of LDS round trips and FP64 divisions of a line (the elimination's are
+// 118 us of 325 at 32x32x16, N = 4; 145 MB of factors take 30).  The quotients
+// that depend on the level alone are formed once per level instead of in the
+// entries' inner loop, D and w come from LDS, and an entry's sum over the
+// levels between is unrolled: 433 -> 325 us.
 template <int N>
 __global__ __launch_bounds__(64) void k_imex_factor(ImexArgs a)
 {
     constexpr int B = 2 * N, W = 2 * B + 1, GW = 2 * N + 1;
+    constexpr int P = N + 1;
     extern __shared__ double sm[];
     const int nk = a.nk, lane = threadIdx.x;
     double *Ab = sm;               // [nk][W]: A_{g m} at g W + m - g + B
     double *Gb = Ab + nk * W;      // [nk][GW]: G_{g m} at g GW + m - g + N
+    // per level: rho_bar, c2 then c2 / s, s, g_n then dt^2 g_n / (rho_bar s), the
+    // denominator of G then kap beta, theta_bar then dt^2 / rho_bar
     double *rb = Gb + nk * GW, *c2 = rb + nk, *sv = c2 + nk, *gn = sv + nk, *kb = gn + nk, *tb = kb + nk;
+    double *D = Ab, *w = Ab + P * P;  // until A is formed: (N+1)(N+2) <= nk W values
+    for (int t = lane; t < P * P; t += 64) D[t] = a.D[t];
+    if (lane < P) w[lane] = a.w[lane];
+    __syncthreads();
     const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
     const int64_t nh = a.nh;
     const LineGeo lg = line_geo<N>(a, L);
@@ -149,23 +173,32 @@ __global__ __launch_bounds__(64) void k_imex_factor(ImexArgs a)
         c2[g] = a.gamma * a.ref[2 * a.nu + I] / a.ref[I];
         tb[g] = a.shell ? a.ref[a.nu + I] : a.theta0;
         level_factors<N>(a, g, sv[g], gn[g]);
-    }
-    for (int t = lane; t < nk * GW; t += 64) {
-        const int g = t / GW, m = g + t % GW - N;
-        Gb[t] = (m >= 0 && m < nk) ? g_entry<N>(a, lg, g, m) : 0.0;
+        kb[g] = g_den<N>(a, lg, w, g);
     }
     __syncthreads();
-    // kap beta at every level, beta = G(theta_bar)
+    for (int t = lane; t < nk * GW; t += 64) {
+        const int g = t / GW, m = g + t % GW - N;
+        Gb[t] = (m >= 0 && m < nk) ? g_num<N>(D, w, nk, g, m) / kb[g] : 0.0;
+    }
+    __syncthreads();
+    // kap beta at every level, beta = G(theta_bar); theta_bar is constant on the box
     for (int g = lane; g < nk; g += 64) {
         double beta = 0.0;
-        for (int d = 0; d < GW; ++d) {
+        for (int d = 0; d < GW && a.shell; ++d) {
             const int m = g + d - N;
             if (m >= 0 && m < nk) beta += Gb[g * GW + d] * tb[m];
         }
-        kb[g] = a.shell ? c2[g] * rb[g] / tb[g] * beta : 0.0;  // theta_bar is constant on the box
+        kb[g] = a.shell ? c2[g] * rb[g] / tb[g] * beta : 0.0;
     }
     __syncthreads();
+    // the quotients that only depend on the level
     const double dt2 = a.dt * a.dt;
+    for (int g = lane; g < nk; g += 64) {
+        c2[g] = c2[g] / sv[g];
+        tb[g] = dt2 / rb[g];
+        gn[g] = dt2 * gn[g] / (rb[g] * sv[g]);
+    }
+    __syncthreads();
     for (int t = lane; t < nk * W; t += 64) {
         const int g = t / W, m = g + t % W - B;
         double v = 0.0;
@@ -175,11 +208,17 @@ __global__ __launch_bounds__(64) void k_imex_factor(ImexArgs a)
             } else {
                 double acc = 0.0;  // (G c2 s^-1 G)_{g m}
                 const int p0 = (g > m ? g : m) - N, p1 = (g < m ? g : m) + N;
-                for (int p = p0 < 0 ? 0 : p0; p <= p1 && p < nk; ++p)
-                    acc += Gb[g * GW + p - g + N] * (c2[p] / sv[p]) * Gb[p * GW + m - p + N];
+#pragma unroll
+                for (int d = -N; d <= N; ++d) {  // one round of LDS reads, not one per term
+                    const int p = g + d;
+                    const bool in = p >= 0 && p >= p0 && p <= p1 && p < nk;
+                    const int pc = in ? p : g;
+                    const double term = Gb[g * GW + pc - g + N] * c2[pc] * Gb[pc * GW + (in ? m - p : 0) + N];
+                    acc = in ? acc + term : acc;
+                }
                 const double gm = (m - g >= -N && m - g <= N) ? Gb[g * GW + m - g + N] : 0.0;
-                v = (m == g ? 1.0 : 0.0) - dt2 / rb[g] * acc * sv[m] * rb[m] - dt2 / rb[g] * gm * kb[m] +
-                    dt2 * gn[g] / (rb[g] * sv[g]) * gm * sv[m] * rb[m];
+                v = (m == g ? 1.0 : 0.0) - tb[g] * acc * sv[m] * rb[m] - tb[g] * gm * kb[m] +
+                    gn[g] * gm * sv[m] * rb[m];
             }
         }
         Ab[t] = v;
@@ -193,15 +232,19 @@ __global__ __launch_bounds__(64) void k_imex_factor(ImexArgs a)
             Ab[r * W + k - r + B] /= Ab[k * W + B];
         }
         __syncthreads();
-        for (int t = lane; t < B * B; t += 64) {
-            const int r = k + 1 + t / B, c = k + 1 + t % B;
-            if (r <= rmax && c <= rmax) Ab[r * W + c - r + B] -= Ab[r * W + k - r + B] * Ab[k * W + c - k + B];
+#pragma unroll
+        for (int s = 0; s < (B * B + 63) / 64; ++s) {
+            const int t = lane + 64 * s, r = k + 1 + t / B, c = k + 1 + t % B;
+            if (t < B * B && r <= rmax && c <= rmax)
+                Ab[r * W + c - r + B] -= Ab[r * W + k - r + B] * Ab[k * W + c - k + B];
         }
         __syncthreads();
     }
     // out, [g][d][line]; entries outside the line are zero, the diagonal is
     // stored as its reciprocal
-    for (int t = lane; t < nk * W; t += 64) a.lu[(int64_t)t * nh + L] = t % W == B ? 1.0 / Ab[t] : Ab[t];
+    for (int g = lane; g < nk; g += 64) Ab[g * W + B] = 1.0 / Ab[g * W + B];
+    __syncthreads();
+    for (int t = lane; t < nk * W; t += 64) a.lu[(int64_t)t * nh + L] = Ab[t];
 }
 
 // D f on one element's nodes (the zeta derivative); D from LDS (uniform
