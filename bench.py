@@ -49,11 +49,11 @@ def element_bytes(nu, nl, prec, metric):
     (rho_bar, theta_bar, p_bar: 3 x 8 B; the recomputed-metric kernels take the
     isentropic theta_bar = theta0 as a constant: 2 x 8 B); per element-local
     node the contribution written once (5 x 8 B, or 5 x 4 B mixed) and, with
-    the stored metric, the 9 inverse-metric entries and J w (10 x 8 B, or
-    10 x 4 B mixed).  Unique ids follow from the lattice and a recomputed
+    the stored metric, its entries that vary on a box (zeta_x, zeta_y, zeta_z
+    and J w: 4 x 8 B, or 4 x 4 B mixed).  Unique ids follow from the lattice and a recomputed
     metric costs no traffic."""
     contrib = 20 if prec == "mixed" else 40
-    met = 0 if metric == "recompute" else (40 if prec == "mixed" else 80)
+    met = 0 if metric == "recompute" else (16 if prec == "mixed" else 32)
     ref = 16 if metric == "recompute" else 24
     return nu * (40 + ref) + nl * (met + contrib)
 
@@ -482,8 +482,9 @@ def main():
             el_ms, el_n, fin_ms, fin_n = g.profile_read()
             g.profile(False)
             el_s, fin_s = el_ms / el_n * 1e-3, fin_ms / fin_n * 1e-3
-            if metric == "recompute" and name == "fp64":  # NUMA_STAGE_AUTO: the split DSS in FP64
+            if name == "fp64":  # NUMA_STAGE_AUTO: the split DSS in FP64
                 ea, fa, _ = split_kernel_bytes(g.n_unique, n_wall, mm["ne"], mm["N"], name)
+                ea += 32 * g.n_local if metric == "stored" else 0  # zeta_x, zeta_y, zeta_z, J w
             else:
                 ea = element_bytes(g.n_unique, g.n_local, name, metric)
                 fa = finish_bytes(g.n_unique, g.n_local, n_wall, name)
