@@ -1906,7 +1906,8 @@ bool split_ok(const Mesh &m, int32_t prec)
 // metric (N: nodes, the routes' times):
 //   FP64 node / gather / split: 1: 25 k 30 / 30 / 45, 524 k 148 / 73 / 74, 1.05 M
 //   272 / 118 / 116; 2: 83 k 34 / 35 / 50, 1.8 M 228 / 156 / 162, 3.5 M 450 /
-//   318 / 284; 3: 197 k 44 / 43 / 51, 524 k 76 / 69 / 73, 786 k 100 / 94 / 90;
+//   318 / 284; 3: 197 k 44 / 43 / 51, 524 k 76 / 69 / 73, 604 k - / 90 /
+//   89, 786 k 100 / 94 / 90;
 //   FP64 node / split: 4: 512 k 82 / 86, 1.02 M 127 / 130, 1.28 M 154 / 141; 5: 885 k
 //   124 / 145, 1.8 M 217 / 225, 2.7 M 346 / 315; 6: 527 k 118 / 125, 615 k 135 / 128;
 //   7: 655 k 120 / 134, 786 k 135 / 139, 1.05 M 153 / 149; 8: 560 k 131 / 153, 746 k
@@ -1919,7 +1920,7 @@ int auto_route(int N, int32_t prec, int64_t nl)
 {
     //                                     N = 1      2       3        4        5       6        7        8
     static const int64_t node64[9] = {0, 28000, 95000, 200000, 600000, 1500000, 500000, 720000, 600000};
-    static const int64_t gather64[4] = {0, 800000, 2300000, 620000};
+    static const int64_t gather64[4] = {0, 800000, 2300000, 560000};
     static const int64_t nodemx[9] = {0, 28000, 90000, 190000, 400000, 1000000, 450000, 2300000, 1800000};
     if (prec == NUMA_PREC_MIXED) return nl < nodemx[N] ? kNode : kGather;
     if (nl < node64[N]) return kNode;

@@ -102,13 +102,13 @@ template <int N, typename T> constexpr int shell_threads()
 // 29 k 43 / 39; 2: 41 k 33 / 40, 97 k 43 / 42; 3: 442 k 77 / 79, 786 k 116 / 107; 4:
 // 450 k 87 / 91, 864 k 139 / 128; 5: 187 k 60 / 67, 332 k 84 / 80; 6: 132 k 54 / 84,
 // 296 k 103 / 95; 7: 442 k 113 / 126, 786 k 170 / 160; 8: 2.6 M 652 / 709 (spills:
-// not taken).  Mixed: 3: 98 k 39 / 45, 230 k 51 / 49; 4: 450 k 72 / 80, 864 k 117 /
-// 114; 5: 778 k 116 / 117, 1.5 M 191 / 168; 6: 132 k 48 / 67, 296 k 84 / 77; 7: 1.8 M
+// not taken).  Mixed: 3: 98 k 39 / 45, 325 k 59 / 61, 376 k 65 / 66, 508 k 77 / 73; 4:
+// 450 k 72 / 80, 864 k 117 / 114; 5: 778 k 116 / 117, 1.5 M 191 / 168; 6: 132 k 48 / 67, 296 k 84 / 77; 7: 1.8 M
 // 245 / 245; 8: 280 k 81 / 94, 630 k 141 / 134.
 template <int N, typename T> constexpr int64_t shell_col_from()
 {
     constexpr int64_t f64[9] = {0, 20000, 90000, 600000, 700000, 300000, 250000, 700000, INT64_MAX};
-    constexpr int64_t f32[9] = {0, 20000, 90000, 200000, 800000, 800000, 250000, 2000000, 500000};
+    constexpr int64_t f32[9] = {0, 20000, 90000, 430000, 800000, 800000, 250000, 2000000, 500000};
     return sizeof(T) == 8 ? f64[N] : f32[N];
 }
 // Element kernel, one node per lane -> columns: 32x32x10 at N = 4 (61,440
