@@ -589,10 +589,11 @@ __global__ __launch_bounds__((col_threads<N, T>()), (col_blocks<N, T, MODE>())) 
 // contractions FP32, rho, 1/rho, rho'/rho and p' formed in FP64 as there);
 // the tail is the split DSS.  FP64: three workgroups per CU at N = 3, 4 (41 and
 // 50 KB of LDS; at N = 3 four would spill 48 bytes: 64x64x16 98 against 85 us),
-// four below; N = 5..8 as noted below.  Mixed (N <= 4): four waves per SIMD.
+// four below; N = 5..8 as noted below.  Mixed: four waves per SIMD below N = 4,
+// three at N = 4 (four spill 48 bytes: step 854 against 789 us).
 template <int N, typename T> constexpr int col2_waves()
 {
-    return sizeof(T) == 4 ? 4 : (N <= 2 ? 4 : (N <= 4 ? 3 : 2));
+    return sizeof(T) == 4 ? (N == 4 ? 3 : 4) : (N <= 2 ? 4 : (N <= 4 ? 3 : 2));
 }
 // doubles after each element's tile: at N = 4, 8 spread the xi and eta rows of
 // the two or three elements a wavefront spans over the LDS banks (50,640
