@@ -416,9 +416,9 @@ __device__ __forceinline__ void split_store(const BatchItem &it, const SplitGeo 
             double r[5], o[5];
 #pragma unroll
             for (int v = 0; v < 5; ++v) {
-                T c = st[(qq * NP + l) * 5 + v];
-                if (ii == 0) c += st[((qq - 1) * NP + lw) * 5 + v];
-                r[v] = (double)c * pf.m[p];
+                double c = (double)st[(qq * NP + l) * 5 + v];
+                if (ii == 0) c += (double)st[((qq - 1) * NP + lw) * 5 + v];
+                r[v] = c * pf.m[p];
             }
             if (fold) {
 #pragma unroll
@@ -1007,8 +1007,9 @@ __global__ __launch_bounds__((split_threads<N>()), 2) void k_elem_rows(Batch B)
 // the interior rows of a run's first element, N nodes per row (i < N): the
 // elements e = c EB (one per element workgroup), then the row starts
 // e = r nx that are not multiples of EB.  Every node's
-// copies are read in a fixed order (z copies, y copies, then the x copies of
-// each), summed in FP64, multiplied by M^-1, projected at the walls and
+// copies are summed in FP64 in a fixed order (the x pair of each (y, z) copy
+// first, then over y and z; in mixed precision a pair inside a run is already
+// one FP32 value of Fa), multiplied by M^-1, projected at the walls and
 // advanced by the stage update (PLAIN: the summed value itself, for the
 // filter: the stage operands are not read).
 template <int N, typename T, bool PLAIN = false>
@@ -1107,7 +1108,7 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
         // together; the run-start x copies (Fb, at most one node in EB N of a
         // row) only where there are any.  The sum: x pairs first, then over y
         // and z, as the gather finish (box_finish_node) takes it
-        T ca[2][2][5];
+        double ca[2][2][5];
 #pragma unroll
         for (int z = 0; z < 2; ++z)
 #pragma unroll
@@ -1115,7 +1116,7 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
                 const bool has = z < nzc && y < nyc;
                 const int64_t o = ((int64_t)(zc[z] * ny + yc[y]) * NFP + split_fp<N>(jc[y], kc[z])) * ni + gi;
 #pragma unroll
-                for (int v = 0; v < 5; ++v) ca[z][y][v] = has ? Fa[o * 5 + v] : (T)0;
+                for (int v = 0; v < 5; ++v) ca[z][y][v] = has ? (double)Fa[o * 5 + v] : 0.0;
             }
         if (xface) {
 #pragma unroll
@@ -1126,7 +1127,7 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
                     if (z < nzc && y < nyc && (ex == 0 || ec % EB == 0)) {
                         const int64_t ob = ((int64_t)(ex == 0 ? ec + nx - 1 : ec - 1) * NB + split_fp<N>(jc[y], kc[z])) * 5;
 #pragma unroll
-                        for (int v = 0; v < 5; ++v) ca[z][y][v] += Fb[ob + v];
+                        for (int v = 0; v < 5; ++v) ca[z][y][v] += (double)Fb[ob + v];
                     }
                 }
         }
@@ -1136,7 +1137,7 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
             for (int y = 0; y < 2; ++y)
                 if (z < nzc && y < nyc)
 #pragma unroll
-                    for (int v = 0; v < 5; ++v) r[v] += (double)ca[z][y][v];
+                    for (int v = 0; v < 5; ++v) r[v] += ca[z][y][v];
     } else {
         if constexpr (NIP == 0) {
             return;
@@ -1167,7 +1168,7 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
                 c1[v] = i == 0 ? Fb[o1 + v] : (T)0;
             }
 #pragma unroll
-            for (int v = 0; v < 5; ++v) r[v] = (double)(c0[v] + c1[v]);  // absent: zero
+            for (int v = 0; v < 5; ++v) r[v] = (double)c0[v] + (double)c1[v];  // absent: zero
         }
     }
 #pragma unroll

@@ -639,11 +639,11 @@ __device__ __forceinline__ void box_finish_node(const PointArgs &p, const BoxFin
                     for (int v = 0; v < 5; ++v) c[2 * y + x][v] = (T)0;
                 }
             }
-        // x pairs first, then over y and z, as the split DSS takes them
+        // in FP64: x pairs first, then over y and z, as the split DSS takes them
 #pragma unroll
         for (int y = 0; y < 2; ++y)
 #pragma unroll
-            for (int v = 0; v < 5; ++v) r[v] += (double)(c[2 * y][v] + c[2 * y + 1][v]);
+            for (int v = 0; v < 5; ++v) r[v] += (double)c[2 * y][v] + (double)c[2 * y + 1][v];
     }
 #pragma unroll
     for (int v = 0; v < 5; ++v) r[v] *= mi;
