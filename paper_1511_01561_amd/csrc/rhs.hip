@@ -82,14 +82,36 @@ __global__ __launch_bounds__(block_threads<N>()) void k_rhs(RhsArgs<T> a, TO *ou
 // (k_rhs above) reads 15 tile values per field and node at N = 4 (27 contractions
 // of 5), forms every node's metric, gravity and reference loads for itself, and
 // waits for one gather at three waves per SIMD.  Here the tile holds p', u, v,
-// w, theta' (momentum and theta' rows), then rho u, rho v, rho w (mass row); the
-// zeta derivatives come from the lane's own column, which it reads once, the
-// column factors of the metric are loaded once per column, and the reference and
-// the layer factors, the same for all nodes of a level, once per level from one
-// address.  theta_bar varies along zeta only.
+// w, theta' (momentum and theta' rows), then rho u, rho v, rho w (mass row; in
+// mixed precision they are formed at the gather, from the FP64 velocity as in
+// k_rhs, and have the FP32 tile's room beside the others); the zeta derivatives
+// come from the lane's own column, which it reads once, the column factors of the
+// metric are loaded once per column, and the reference and the layer factors, the
+// same for all nodes of a level, once per level from one address.  theta_bar varies
+// along zeta only.
+//
+// Waves per SIMD the registers are held to, and elements per workgroup: as many as
+// four wavefronts and the workgroup's share of the LDS at that occupancy hold.
+template <int N, typename T> constexpr int shell_waves() { return sizeof(T) == 8 ? 2 : N <= 4 ? 4 : N <= 6 ? 3 : 2; }
+// Fluxes in the slots of the fields before them: FP64, and mixed N = 6, where eight
+// fields leave room for four elements in place of five (step at 6x12x12x8 274 against
+// 271 us; there the fluxes wait in registers, 32 bytes of spill a lane).
+template <int N, typename T> constexpr bool shell_two_pass() { return sizeof(T) == 8 || N == 6; }
+template <int N, typename T> constexpr int shell_fields() { return shell_two_pass<N, T>() ? 5 : 8; }  // of the tile
+// Values after an element's tile that spread the elements of a wavefront over the LDS
+// banks.  Mixed: one element's columns follow the other's in the 64 banks (at N = 1
+// every element starts at the same bank otherwise: step at 6x60x60x10 201 against
+// 150 us); at N = 4 that takes a workgroup off the CU.
+template <int N, typename T> constexpr int shell_pad()
+{
+    constexpr int PP = (N + 1) * (N + 1), over = (shell_fields<N, T>() * PP * (N + 1) - PP) % 64;
+    return sizeof(T) == 8 ? (N == 4 ? 8 : 0) : N == 4 ? 0 : (64 - over) % 64;
+}
 template <int N, typename T> constexpr int shell_eb()
 {
-    constexpr int PP = (N + 1) * (N + 1), lanes = 256 / PP, lds = 81920 / (5 * PP * (N + 1) * (int)sizeof(T));
+    constexpr int PP = (N + 1) * (N + 1), lanes = 256 / PP;
+    constexpr int tile = (shell_fields<N, T>() * PP * (N + 1) + shell_pad<N, T>()) * (int)sizeof(T);
+    constexpr int lds = 163840 / shell_waves<N, T>() / tile;
     return lanes < lds ? lanes : lds;
 }
 template <int N, typename T> constexpr int shell_threads()
@@ -115,15 +137,16 @@ template <int N, typename T> constexpr int64_t shell_col_from()
 // elements) FP64 304 -> 234 us, mixed 221 -> 155; N = 2 83 -> 37; 20x20x8 at N = 5
 // 215 -> 137, mixed 133 -> 93; 16x16x8 at N = 6 273 -> 170, mixed 191 -> 101; 14x14x8
 // at N = 7 299 -> 205; mixed 12x12x8 at N = 8 255 -> 157.  Waves per SIMD: FP64 at
-// N = 4 three spill 128 bytes (282 against 234 us); mixed at N = 4 four with 16 bytes
-// of spill 155 against 170 us with three.
-template <int N, typename T> constexpr int shell_waves() { return sizeof(T) == 8 ? 2 : N <= 4 ? 4 : N == 5 ? 3 : 2; }
+// N = 4 three spill 128 bytes (282 against 234 us).
 template <int N, typename T>
 __global__ __launch_bounds__((shell_threads<N, T>()), (shell_waves<N, T>())) void k_shell_col(RhsArgs<T> a, int ne, T *out)
 {
     constexpr int P = N + 1, PP = P * P, NP = PP * P, EB = shell_eb<N, T>(), BT = shell_threads<N, T>();
-    constexpr int PAD = sizeof(T) == 8 && N == 4 ? 8 : 0;  // spreads the lines over the LDS banks
-    __shared__ __align__(16) T s[EB][5 * NP + PAD];
+    constexpr bool F64 = sizeof(T) == 8;
+    constexpr bool EARLY = F64 || N < 4 || N == 8;
+    constexpr bool TWO = shell_two_pass<N, T>();
+    constexpr int FL = TWO ? 0 : 5;  // tile slot of the mass fluxes
+    __shared__ __align__(16) T s[EB][shell_fields<N, T>() * NP + shell_pad<N, T>()];
     const int e0 = (int)xcd_remap(blockIdx.x, gridDim.x) * EB;
     const int t = threadIdx.x, q = t / PP, c = t % PP, i = c % P, j = c / P;
     const bool act = q < EB && e0 + q < ne;
@@ -137,7 +160,7 @@ __global__ __launch_bounds__((shell_threads<N, T>()), (shell_waves<N, T>())) voi
     // of the column: metric factors (xi, eta, zeta rows), J w, direction; of its
     // nodes: rho, 1/rho, rho' (FP64) or rho'/rho
     double F[9], jwc = 0.0, dn[3], rho[P];
-    T ir[P], bq[P], tb[P];
+    T ir[P], bq[P], tb[P], fl[P][3];
     int ez = 0;
     const double *lay = a.slay;
     if (act) {
@@ -145,11 +168,17 @@ __global__ __launch_bounds__((shell_threads<N, T>()), (shell_waves<N, T>())) voi
         const int eh = e0 + q - ez * (int)a.feh.d;
         lay = a.slay + 4 * ez * P;
         const double *cp = a.scol + (int64_t)eh * (13 * PP) + c;
+        auto factors = [&]() {
 #pragma unroll
-        for (int d = 0; d < 9; ++d) F[d] = cp[d * PP];
-        jwc = cp[9 * PP];
+            for (int d = 0; d < 9; ++d) F[d] = cp[d * PP];
+            jwc = cp[9 * PP];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) dn[d] = cp[(10 + d) * PP];
+            for (int d = 0; d < 3; ++d) dn[d] = cp[(10 + d) * PP];
+        };
+        // before the gather, or behind it where their 26 registers beside its
+        // values cost more than the wait (mixed N = 4 spills 48 bytes with them,
+        // N = 6 loses a wave: step at 6x12x12x8 271 against 324 us)
+        if constexpr (EARLY) factors();
         const int64_t level = a.nh * ((int64_t)ez * N);
         const double *qp = a.q + (level + a.shid[eh * PP + c]), *rf = a.ref + level;
         double qv[P][5], rb[P], tbk[P], pb[P], x[P], pp[P];
@@ -167,14 +196,25 @@ __global__ __launch_bounds__((shell_threads<N, T>()), (shell_waves<N, T>())) voi
             rho[k] = rb[k] + qv[k][0];
             const double ird = 1.0 / rho[k];
             ir[k] = (T)ird;
-            bq[k] = sizeof(T) == 8 ? (T)qv[k][0] : (T)(qv[k][0] * ird);
+            bq[k] = F64 ? (T)qv[k][0] : (T)(qv[k][0] * ird);
             tb[k] = (T)(tbk[k] - tbk[0]);
 #pragma unroll
             for (int v = 1; v < 5; ++v) S[v * NP + c + PP * k] = (T)qv[k][v];
+            if (!F64)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const T f = (T)(rho[k] * qv[k][1 + b]);
+                    if (TWO) fl[k][b] = f;
+                    else S[(FL + b) * NP + c + PP * k] = f;
+                }
         }
         eos_nodes<P>(P, x, pb, a.gamma, a.eos, pp);
 #pragma unroll
         for (int k = 0; k < P; ++k) S[c + PP * k] = (T)pp[k];
+        if constexpr (!EARLY) {
+            __builtin_amdgcn_sched_barrier(0);
+            factors();
+        }
     }
     auto metric = [&](int k, T *mx) {
         const double r = lay[4 * k], z = lay[4 * k + 1];
@@ -208,33 +248,35 @@ __global__ __launch_bounds__((shell_threads<N, T>()), (shell_waves<N, T>())) voi
             }
             R[4] -= U[2] * dot<P>(a.D + k * P, [&](int m) { return tb[m]; });
             derive(0, k, d);
-            const T bk = sizeof(T) == 8 ? bq[k] * ir[k] : bq[k];
+            const T bk = F64 ? bq[k] * ir[k] : bq[k];
             const double ga = -lay[4 * k + 3];
 #pragma unroll
             for (int b = 0; b < 3; ++b)
                 R[1 + b] += bk * (T)(ga * dn[b]) - (d[0] * mx[b] + d[1] * mx[3 + b] + d[2] * mx[6 + b]) * ir[k];
-            const bool fold = sizeof(T) == 8 && folds(k);
+            const bool fold = F64 && folds(k);
 #pragma unroll
             for (int v = 1; v < 5; ++v) res[k][v] = mx[9] * (fold ? fma(cdt, R[v], qv[v]) : R[v]);
             __builtin_amdgcn_sched_barrier(0);  // a node's lines at a time: registers
         }
     }
-    // the mass fluxes, formed from the first tile
-    T fl[P][3];
-    if (act) {
+    // the mass fluxes (FP64: formed from the first tile)
+    if (act && (F64 || !TWO)) {
 #pragma unroll
         for (int k = 0; k < P; ++k)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) fl[k][b] = (T)(rho[k] * (double)S[(1 + b) * NP + c + PP * k]);
+            for (int b = 0; b < 3; ++b)
+                fl[k][b] = F64 ? (T)(rho[k] * (double)S[(1 + b) * NP + c + PP * k]) : S[(FL + b) * NP + c + PP * k];
     }
-    __syncthreads();  // first tile read
-    if (act) {
+    if constexpr (TWO) {
+        __syncthreads();  // first tile read
+        if (act) {
 #pragma unroll
-        for (int k = 0; k < P; ++k)
+            for (int k = 0; k < P; ++k)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) S[b * NP + c + PP * k] = fl[k][b];
+                for (int b = 0; b < 3; ++b) S[(FL + b) * NP + c + PP * k] = fl[k][b];
+        }
+        __syncthreads();  // second tile complete
     }
-    __syncthreads();  // second tile complete
     if (act) {
 #pragma unroll
         for (int k = 0; k < P; ++k) {
@@ -243,17 +285,17 @@ __global__ __launch_bounds__((shell_threads<N, T>()), (shell_waves<N, T>())) voi
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
                 T d[3];
-                d[0] = dot<P>(Di, [&](int m) { return S[b * NP + m + P * (j + P * k)]; });
-                d[1] = dot<P>(Dj, [&](int m) { return S[b * NP + i + P * (m + P * k)]; });
+                d[0] = dot<P>(Di, [&](int m) { return S[(FL + b) * NP + m + P * (j + P * k)]; });
+                d[1] = dot<P>(Dj, [&](int m) { return S[(FL + b) * NP + i + P * (m + P * k)]; });
                 d[2] = dot<P>(a.D + k * P, [&](int m) { return fl[m][b]; });
                 dv += d[0] * mx[b] + d[1] * mx[3 + b] + d[2] * mx[6 + b];
             }
-            const bool fold = sizeof(T) == 8 && folds(k);
+            const bool fold = F64 && folds(k);
             res[k][0] = mx[9] * (fold ? fma(cdt, -dv, bq[k]) : -dv);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    __syncthreads();  // second tile read
+    __syncthreads();  // fluxes read
     T *st = &s[0][0];
     if (act) {
 #pragma unroll
