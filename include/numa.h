@@ -314,7 +314,8 @@ int32_t numa_rk_stage(numa_mesh_t m, int32_t stage, double dt, const double *qn,
  * on the box the element kernel already sums the copies inside its run of
  * elements and finishes those nodes, and writes only the others' copies for
  * the finish kernel).  In FP64 (box and shell; not NUMA_STAGE_GATHER on the box at
- * N = 5, 6 with the recomputed metric) the contribution
+ * N = 5, 6 with the recomputed metric, nor a box with the stored metric whose x
+ * element count numa_step_batch does not take) the contribution
  * away from the walls is J w (q_s + c dt R), so that the finish need not read
  * q_s there; with the recomputed metric M is then the sum of the recomputed
  * J w.  Uses the workspace scratch; equals the composition of numa_rhs,

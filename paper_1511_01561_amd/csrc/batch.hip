@@ -1562,8 +1562,12 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
     const int eb = split ? split_eb<N>() : col ? col_eb<N, T>() : 1;
     // FP64 update that uses q_s (b != 0): the column and one-node-per-lane
     // element kernels fold q_s into the contributions (the streaming one,
-    // which runs at its register limit, does not)
-    B.fold = (std::is_same<T, double>::value && B.cb != 0.0 && (split || !(col && kind == 1))) ? 1 : 0;
+    // which runs at its register limit, does not).  The weighted sum of the fold
+    // rounds q_s once per copy (against 64-bit evaluation, N = 2: 1.4e-16 where
+    // the update alone leaves 7.3e-17).  With the stored metric, on x extents
+    // that numa_step_batch does not take (one item), the finish reads q_s instead.
+    B.fold = std::is_same<T, double>::value && B.cb != 0.0 && (split || !(col && kind == 1)) &&
+             (recompute || box_batchable(*items[0].mesh));
     int64_t eo = 0, bo = 0;
     for (int k = 0; k < n; ++k) {
         const Mesh &m = *items[k].mesh;
