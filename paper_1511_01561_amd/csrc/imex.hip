@@ -574,6 +574,16 @@ __device__ __forceinline__ void derive(const ImexArgs &a, const double (&f)[N + 
     }
 }
 
+// The Robert-Asselin value of the box's rho' and w at the end takes q^n and q^{n-1}
+// from registers, or reads them again where those registers cost more than the
+// reads (kept / read again, us per step): N = 5, 32x32x16 464 / 379 (two waves per
+// SIMD or one), 16x16x17 133 / 132; N = 7, 16x16x17 535 / 469, but 32x32x8 595 / 612;
+// N = 8, 16x16x8 257 / 251, but 16x16x17 930 / 1,116; N <= 4 mostly 1 to 3 %
+// slower read again, N = 6 equal.
+template <int N, int MAXT> constexpr bool imex_keeps()
+{
+    return !(N == 5 || (N == 7 && MAXT == 512) || (N == 8 && MAXT == 256));
+}
 template <int N, bool SHELL, int MAXT>
 __global__ __launch_bounds__(MAXT) void k_imex_lines(ImexArgs a)
 {
@@ -602,7 +612,7 @@ __global__ __launch_bounds__(MAXT) void k_imex_lines(ImexArgs a)
         if (k == 0 && e > 0) return (wN * Ex[(e - 1) * kLines + line] + w0 * dk) * gi[0];
         return dk * gi[k];
     };
-    double rr[P], rt[P], be[P], sd0[P], swv[P], rw[P], t0[P], tw[P];
+    double rr[P], rt[P], be[P], sd0[P], swv[P], rw[P], qr[P], qw3[P];
     double df[P], dh[P], dtb[P];
     if (act) {
         double f[P], h[P], tb[P];
@@ -628,9 +638,8 @@ __global__ __launch_bounds__(MAXT) void k_imex_lines(ImexArgs a)
                 sv[k] = 1.0;
                 gn[k] = a.gz;
                 gi[k] = lg.izz;
-                // Robert-Asselin: q + ra (q_prev - 2 q + q_new) with the new value added at the end
-                t0[k] = fma(ra, p0 - 2.0 * c0, c0);
-                tw[k] = fma(ra, p3 - 2.0 * c3, c3);
+                qr[k] = c0;  // for the Robert-Asselin values at the end
+                qw3[k] = c3;
             }
             f[k] = sv[k] * rb[k] * swv[k];
             h[k] = cc[k] * sd0[k] + kp[k] * (2.0 * c4 - p4);
@@ -742,10 +751,14 @@ __global__ __launch_bounds__(MAXT) void k_imex_lines(ImexArgs a)
                     a.qcur[v * nu + I] = nv[v];
                 }
             } else {
-                a.qprev[I] = fma(ra, nr, t0[k]);
+                constexpr bool KEEP = imex_keeps<N, MAXT>();
+                const int64_t J = 3 * nu + I;
+                const double c0 = KEEP ? qr[k] : a.qcur[I], c3 = KEEP ? qw3[k] : a.qcur[J];
+                const double d0 = KEEP ? sd0[k] : 2.0 * c0 - a.qprev[I], d3 = KEEP ? swv[k] : 2.0 * c3 - a.qprev[J];
+                a.qprev[I] = c0 + ra * (nr - d0);
                 a.qcur[I] = nr;
-                a.qprev[3 * nu + I] = fma(ra, w, tw[k]);
-                a.qcur[3 * nu + I] = w;
+                a.qprev[J] = c3 + ra * (w - d3);
+                a.qcur[J] = w;
             }
         }
 }
