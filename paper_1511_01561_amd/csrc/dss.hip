@@ -18,8 +18,7 @@ using namespace dev;
 // face, wrapped where periodic), the shell's are its horizontal copies in the
 // bottom layer (hoff/hidx) in each radial layer that holds its level.  Nothing
 // but the copies themselves is read (the shell: its short horizontal list), where
-// the inverse map costs 4 bytes per copy and puts a load in front of every copy
-// (17x13x7, N = 5: 14.5 -> 11.2 us).
+// the inverse map costs 4 bytes per copy and puts a load in front of every copy.
 struct DssGeo {
     FastDiv fi, fj;            // box: division by ni and nj; shell: fi by n_horiz
     int nx, ny, nz, walls;     // elements; shell: nz layers
@@ -83,40 +82,73 @@ __device__ __forceinline__ void node_copies(const DssGeo &g, uint32_t I, int *cc
     }
 }
 
-template <int N, bool SHELL>
-__global__ __launch_bounds__(256) void k_dss(PointArgs p, DssGeo g, int nvar, const double *cin, double *out, int flags)
+// A lane per node and NV variables; the blocks (fb per group of variables, the
+// first variable `first`) run through the nodes of one group after the other.
+// Bound by memory latency: what counts is waves with loads in flight.  NV = 1 takes
+// 46 registers (five variables and all their copies in a lane took 174, two waves
+// per SIMD: one variable at N = 7, 1.2 M element-local nodes, 18.6 us).  Shells from
+// 300,000 element-local nodes on share a lane's list and addresses among up to five
+// variables, four copies of each in flight (62 registers).  us, by the inverse map with
+// its copies one after another / NV = 1 / up to 5, for 1 and 5 variables: box
+// 64x64x16 N = 4 56 / 32 / 32, 327 / 209 / 253; box 17x13x7 N = 5 4.8 / 4.0 / 4.0,
+// 12.0 / 8.5 / 7.2; shell 6x14x14x5 N = 5 9.4 / 7.7 / 7.7, 34.6 / 31.8 / 25.7; shell
+// 6x4x4x4 N = 4 4.5 / 3.5 / 3.5, 10.1 / 4.3 / 5.0.
+template <int N, bool SHELL, int NV>
+__global__ __launch_bounds__(256) void k_dss(PointArgs p, DssGeo g, FastDiv fb, int first, int nvar, const double *cin,
+                                             double *out, int flags)
 {
-    const int64_t I = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    const uint32_t group = fdiv(blockIdx.x, fb), b = (uint32_t)xcd_remap(blockIdx.x - group * fb.d, fb.d);
+    const int64_t I = (int64_t)b * 256 + threadIdx.x;
     if (I >= p.nu) return;
+    const int v0 = first + (int)group * NV, nv = nvar - v0 < NV ? nvar - v0 : NV;
+    const bool wall = (flags & NUMA_DSS_NOFLUX) && p.walls && (I < p.nh || I >= p.nu - p.nh);
+    // the projection needs three components: one lane of NV = 1 forms them all
+    if (NV == 1 && wall && (v0 == 2 || v0 == 3)) return;
     int cc[8];
     node_copies<N, SHELL>(g, (uint32_t)I, cc);
-    double r[5] = {0, 0, 0, 0, 0};
-    const bool mass = flags & NUMA_DSS_MASS;
-    const double mi = mass ? p.Minv[I] : 1.0;
-    for (int v0 = 0; v0 < nvar; v0 += 5) {
-        const int nv = nvar - v0 < 5 ? nvar - v0 : 5;
-        // absent copies are not loaded; the present ones are added in ascending order
-        double c[8][5];
+    const double mi = flags & NUMA_DSS_MASS ? p.Minv[I] : 1.0;
+    double r[NV];
+    // absent copies are not loaded; the present ones are added in ascending order
+    auto sum = [&](const double *src, double *r) {
+        constexpr int Z = NV == 1 ? 8 : 4;  // copies in flight
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
+        for (int v = 0; v < NV; ++v) r[v] = 0.0;
 #pragma unroll
-            for (int v = 0; v < 5; ++v)
-                c[k][v] = cc[k] >= 0 && v < nv ? cin[(v0 + v) * p.nl + cc[k]] : 0.0;
+        for (int k0 = 0; k0 < 8; k0 += Z) {
+            if (k0 > 0 && cc[k0] < 0) break;  // a second layer has a first copy
+            double c[Z][NV];
 #pragma unroll
-        for (int v = 0; v < 5; ++v) r[v] = 0.0;
+            for (int k = 0; k < Z; ++k)
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (cc[k] >= 0)
+                for (int v = 0; v < NV; ++v) c[k][v] = cc[k0 + k] >= 0 && v < nv ? src[v * p.nl + cc[k0 + k]] : 0.0;
 #pragma unroll
-                for (int v = 0; v < 5; ++v) r[v] += c[k][v];
-        if (mass)
+            for (int k = 0; k < Z; ++k)
+                if (cc[k0 + k] >= 0)
 #pragma unroll
-            for (int v = 0; v < 5; ++v) r[v] *= mi;
-        if ((flags & NUMA_DSS_NOFLUX) && nvar == 5) noflux(p, I, r[1], r[2], r[3]);
+                    for (int v = 0; v < NV; ++v) r[v] += c[k][v];
+        }
+        if (flags & NUMA_DSS_MASS)
 #pragma unroll
-        for (int v = 0; v < 5; ++v)
-            if (v < nv) out[(v0 + v) * p.nu + I] = r[v];
+            for (int v = 0; v < NV; ++v) r[v] *= mi;
+    };
+    const double *src = cin + v0 * p.nl;
+    double *dst = out + v0 * p.nu + I;
+    sum(src, r);
+    if constexpr (NV == 1) {
+        if (wall && v0 == 1) {
+            double r2, r3;
+            sum(src + p.nl, &r2);
+            sum(src + 2 * p.nl, &r3);
+            noflux(p, I, r[0], r2, r3);
+            dst[p.nu] = r2;
+            dst[2 * p.nu] = r3;
+        }
+    } else if constexpr (NV == 5) {
+        if (wall) noflux(p, I, r[1], r[2], r[3]);
     }
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        if (v < nv) dst[v * p.nu] = r[v];
 }
 
 __global__ void k_rk_stage(int64_t n, StageCoef c, const double *qn, const double *qs, const double *r,
@@ -261,13 +293,28 @@ int32_t launch_dss(Mesh &m, int32_t nvar, const double *cin, double *out, int32_
     g.hoff = m.dv.hoff;
     g.hidx = m.dv.hidx;
     g.layer = shell ? 6 * m.d.ne[0] * m.d.ne[0] * m.np : 0;
-    const dim3 grid(nblocks(m.nu, 256)), block(256);
+    const uint32_t nb = nblocks(m.nu, 256);
+    const FastDiv fb = fast_div(nb);
+    const int nv = shell && m.nl >= 300000 ? (nvar < 5 ? nvar : 5) : 1;
+    const int groups = (nvar + nv - 1) / nv, most = (int)(((1u << 24) - 1) / nb);  // fewer than 2^32 lanes a launch
+    auto launch_nv = [&](auto order, auto vars) {
+        constexpr int N = decltype(order)::value, NV = decltype(vars)::value;
+        for (int g0 = 0; g0 < groups; g0 += most) {
+            const dim3 grid(nb * (unsigned)(groups - g0 < most ? groups - g0 : most));
+            if (shell)
+                hipLaunchKernelGGL((k_dss<N, true, NV>), grid, dim3(256), 0, s, p, g, fb, g0 * NV, nvar, cin, out, flags);
+            else if constexpr (NV == 1)
+                hipLaunchKernelGGL((k_dss<N, false, 1>), grid, dim3(256), 0, s, p, g, fb, g0, nvar, cin, out, flags);
+        }
+    };
     auto launch = [&](auto order) {
-        constexpr int N = decltype(order)::value;
-        if (shell)
-            hipLaunchKernelGGL((k_dss<N, true>), grid, block, 0, s, p, g, nvar, cin, out, flags);
-        else
-            hipLaunchKernelGGL((k_dss<N, false>), grid, block, 0, s, p, g, nvar, cin, out, flags);
+        switch (nv) {
+        case 1: launch_nv(order, std::integral_constant<int, 1>{}); break;
+        case 2: launch_nv(order, std::integral_constant<int, 2>{}); break;
+        case 3: launch_nv(order, std::integral_constant<int, 3>{}); break;
+        case 4: launch_nv(order, std::integral_constant<int, 4>{}); break;
+        default: launch_nv(order, std::integral_constant<int, 5>{}); break;
+        }
     };
     switch (m.N) {
     case 1: launch(std::integral_constant<int, 1>{}); break;
