@@ -1381,10 +1381,11 @@ struct FilterSplit {
     BatchItem it;             // qs: the state read, qout: the state written (the same array)
     double w[kMaxP];          // GLL weights
     double F[kMaxP * kMaxP];  // 1D nodal filter matrix F[i * (N+1) + m]
-    const double *met;        // stored metric (J w is entry 9), or null: J w = c0 w_k
+    const double *met;        // stored metric (J w is entry 9)
 };
 
-template <int N>
+// STORED: J w of the stored metric, else c0 w_k
+template <int N, bool STORED>
 __global__ __launch_bounds__((split_threads<N>())) void k_filter_col(FilterSplit A)
 {
     constexpr int P = N + 1, PP = P * P, NP = PP * P, EB = split_eb<N>(), BT = split_threads<N>();
@@ -1414,10 +1415,9 @@ __global__ __launch_bounds__((split_threads<N>())) void k_filter_col(FilterSplit
     double jw[P];
     if (act) {
         const BoxElem be = box_elem((uint32_t)(e0 + q), it.fx, it.fy);
-        const bool stored = A.met != nullptr;
-        const double *jp = stored ? A.met + ((int64_t)(e0 + q) * 10 + 9) * NP + c
+        const double *jp = STORED ? A.met + ((int64_t)(e0 + q) * 10 + 9) * NP + c
                                   : it.hcol + (int64_t)(be.ex + gm.nx * be.ey) * (4 * PP) + c;
-        const double c0 = stored ? 0.0 : jp[0];
+        const double c0 = jp[0];
         int gi = be.ex * N + i, gj = be.ey * N + j;
         if (gi == gm.ni) gi = 0;
         if (gj == gm.nj) gj = 0;
@@ -1429,7 +1429,7 @@ __global__ __launch_bounds__((split_threads<N>())) void k_filter_col(FilterSplit
             const int32_t I = base + layer * gk;
 #pragma unroll
             for (int v = 0; v < 5; ++v) S(q, v, c + PP * k) = it.qs[I + v * gm.nu];
-            jw[k] = stored ? jp[PP * k] : c0 * A.w[k];
+            jw[k] = STORED ? jp[PP * k] : c0 * A.w[k];
         }
     }
     __syncthreads();
@@ -1849,8 +1849,12 @@ int32_t run_filter_split(const Mesh &m, const double *F, double *q, hipStream_t 
     const int64_t bo = split_item(m, EB, it);
     for (int k = 0; k <= N; ++k) A.w[k] = m.w[k];
     for (int k = 0; k < (N + 1) * (N + 1); ++k) A.F[k] = F[k];
-    A.met = m.metric_mode == NUMA_METRIC_RECOMPUTE ? nullptr : m.dv.met;
-    hipLaunchKernelGGL((k_filter_col<N>), dim3((unsigned)((m.ne + EB - 1) / EB)), dim3(split_threads<N>()), 0, s, A);
+    A.met = m.dv.met;
+    const dim3 grid((unsigned)((m.ne + EB - 1) / EB)), block(split_threads<N>());
+    if (m.metric_mode == NUMA_METRIC_STORED)
+        hipLaunchKernelGGL((k_filter_col<N, true>), grid, block, 0, s, A);
+    else
+        hipLaunchKernelGGL((k_filter_col<N, false>), grid, block, 0, s, A);
     // the face nodes: the split finish with the identity update (a = b = 0, cdt = 1)
     Batch B{};
     B.n = 1;
