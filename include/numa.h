@@ -224,7 +224,8 @@ int32_t numa_mesh_set_metric(numa_mesh_t m, int32_t mode);
  *   (the element faces in y and z, and the run-start faces) go to the
  *   workspace scratch in rows along x, and a second kernel gathers them and
  *   finishes those nodes.  FP64 N = 1..8 (runs of 64, 28, 16, 10, 7, 5, 4, 2
- *   elements), mixed precision N <= 4 with the recomputed metric; the stage
+ *   elements), mixed precision N <= 4 with the recomputed metric (with the stored
+ *   metric from the size on from which NUMA_STAGE_AUTO takes it); the stage
  *   may write its input state (the nodes the element kernel finishes are
  *   read by no other workgroup).
  * NUMA_STAGE_AUTO (default): what was measured fastest for the precision and

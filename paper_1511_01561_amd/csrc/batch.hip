@@ -1869,9 +1869,25 @@ int32_t run_filter_split(const Mesh &m, const double *F, double *q, hipStream_t 
 
 }  // namespace
 
+// The mesh leaves the way its stages run to the launch's size: NUMA_STAGE_AUTO,
+// and NUMA_STAGE_SPLIT with the stored metric (a small launch takes twice as long
+// through the split DSS as with one node per lane: 51 k nodes at N = 7 89 against 39
+// us a step).
+static bool stage_by_size(const Mesh &m)
+{
+    return m.stage_mode == NUMA_STAGE_AUTO ||
+           (m.stage_mode == NUMA_STAGE_SPLIT && m.metric_mode == NUMA_METRIC_STORED);
+}
+
 bool filter_split_ok(const Mesh &m)
 {
-    return split_ok(m, NUMA_PREC_FP64);
+    // few nodes: one per lane and the gather finish, whose chains are shorter
+    // (as in a stage; both give the same result).  Pair at N = 4: 8 k nodes 10.5
+    // against 15.7 us, 128 k 12.1 / 16.0, 512 k 23.0 / 22.3, 1.02 M 36.3 / 34.2;
+    // N = 8: 47 k 14.1 / 24.1, 373 k 27.8 / 30.0, 746 k 40.9 / 40.0.  With the stored
+    // metric at N = 8 the gather at every size: 1.14 M 56.0 / 63.0
+    if (!split_ok(m, NUMA_PREC_FP64)) return false;
+    return !stage_by_size(m) || (m.nl >= 450000 && !(m.N == 8 && m.metric_mode == NUMA_METRIC_STORED));
 }
 
 int32_t launch_filter_split(const Mesh &m, const double *F, double *q, hipStream_t s)
@@ -1954,13 +1970,13 @@ int32_t launch_batch_stage(const StepItem *items, int n, int32_t prec, int phase
 {
     // items the fused block kernels take (pencil.hip), the colour passes, the
     // split DSS, the rest, the small ones; partitioned in chunks on the stack,
-    // with no host allocation.  The items of NUMA_STAGE_AUTO choose together,
-    // by what they add up to: either way gives an item the same result.
+    // with no host allocation.  The items that go by size choose together, by
+    // what they add up to: either way gives an item the same result.
     constexpr int kChunk = 4 * kMaxBatch;
     StepItem part[5][kChunk];
     int64_t nl = 0;
     for (int k = 0; k < n; ++k)
-        if (items[k].mesh->stage_mode == NUMA_STAGE_AUTO) nl += items[k].mesh->nl;
+        if (stage_by_size(*items[k].mesh)) nl += items[k].mesh->nl;
     for (int c0 = 0; c0 < n; c0 += kChunk) {
         const int cn = n - c0 < kChunk ? n - c0 : kChunk;
         int cnt[5] = {0, 0, 0, 0, 0};
@@ -1968,7 +1984,7 @@ int32_t launch_batch_stage(const StepItem *items, int n, int32_t prec, int phase
             const Mesh &m = *items[k].mesh;
             const int g = pencil_stage_ok(items[k], prec)       ? 4
                           : colour_ok(m)                        ? kColour
-                          : m.stage_mode != NUMA_STAGE_AUTO     ? (split_ok(m, prec) ? kSplit : kGather)
+                          : !stage_by_size(m)                   ? (split_ok(m, prec) ? kSplit : kGather)
                           : m.metric_mode == NUMA_METRIC_STORED ? auto_route_stored(m.N, prec, nl)
                                                                 : auto_route(m.N, prec, nl);
             part[g][cnt[g]++] = items[k];

@@ -224,12 +224,7 @@ int32_t launch_filter(Mesh &m, double order, int32_t cutoff, double *q, hipStrea
     }
     for (int k = 0; k < m.P; ++k) a.w[k] = m.w[k];
     filter_matrix(m.N, m.xi, m.w, order, cutoff, a.F);
-    // few nodes: one per lane and the gather finish, whose chains are shorter
-    // (as in a stage; both give the same result).  Pair at N = 4: 8 k nodes 10.5
-    // against 15.7 us, 128 k 12.1 / 16.0, 512 k 23.0 / 22.3, 1.02 M 36.3 / 34.2;
-    // N = 8: 47 k 14.1 / 24.1, 373 k 27.8 / 30.0, 746 k 40.9 / 40.0
-    const bool small = m.stage_mode == NUMA_STAGE_AUTO && m.nl < 450000;
-    if (!shell && filter_split_ok(m) && !small) return launch_filter_split(m, a.F, q, s);
+    if (!shell && filter_split_ok(m)) return launch_filter_split(m, a.F, q, s);
     const int geo = shell ? kGeoStored : (m.metric_mode == NUMA_METRIC_RECOMPUTE ? kGeoBoxCol : kGeoBox);
     // the box and the shell sum the contributions with their stage finish kernels
     switch (m.N) {

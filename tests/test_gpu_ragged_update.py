@@ -10,9 +10,9 @@ from test_gpu_parity import torch_cuda  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 # below and above the size from which the stored metric's stages take the split DSS
-BOXES = [(1, (7, 3, 2)), (1, (149, 60, 2)), (2, (5, 2, 3)), (2, (70, 41, 4)), (3, (21, 2, 2)), (3, (50, 27, 4)),
-         (4, (6, 4, 2)), (4, (50, 25, 5)), (5, (7, 2, 2)), (5, (47, 33, 4)), (6, (5, 2, 2)), (6, (29, 27, 2)),
-         (7, (3, 2, 2)), (7, (39, 20, 2)), (8, (3, 2, 2)), (8, (31, 15, 2))]
+BOXES = [(1, (7, 3, 2)), (1, (149, 61, 3)), (2, (5, 2, 3)), (2, (109, 105, 5)), (3, (21, 2, 2)), (3, (53, 49, 5)),
+         (4, (6, 4, 2)), (4, (45, 41, 5)), (5, (7, 2, 2)), (5, (46, 41, 6)), (6, (5, 2, 2)), (6, (31, 27, 3)),
+         (7, (3, 2, 2)), (7, (31, 31, 4)), (8, (3, 2, 2)), (8, (29, 28, 5))]
 
 
 @pytest.mark.parametrize("N,ne", BOXES)
