@@ -1007,9 +1007,8 @@ __global__ __launch_bounds__((split_threads<N>()), 2) void k_elem_rows(Batch B)
 // the interior rows of a run's first element, N nodes per row (i < N): the
 // elements e = c EB (one per element workgroup), then the row starts
 // e = r nx that are not multiples of EB.  Every node's
-// copies are summed in FP64 in a fixed order (the x pair of each (y, z) copy
-// first, then over y and z; in mixed precision a pair inside a run is already
-// one FP32 value of Fa), multiplied by M^-1, projected at the walls and
+// copies are summed in FP64 in a fixed order (in mixed precision a pair inside a
+// run is already one FP32 value of Fa), multiplied by M^-1, projected at the walls and
 // advanced by the stage update (PLAIN: the summed value itself, for the
 // filter: the stage operands are not read).
 template <int N, typename T, bool PLAIN = false>
@@ -1107,8 +1106,12 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
         // the face rows' copies (absent ones are not loaded) are loaded
         // together; the run-start x copies (Fb, at most one node in EB N of a
         // row) only where there are any.  The sum: x pairs first, then over y
-        // and z, as the gather finish (box_finish_node) takes it
-        double ca[2][2][5];
+        // and z, as the gather finish (box_finish_node) takes it.  In mixed
+        // precision, whose pairs inside a run are sums already, the run-start
+        // copies come last (the pairs in FP64 first: 3.5 us more at 1.2 M nodes,
+        // N = 4, for a wave less)
+        constexpr bool PAIRS = sizeof(T) == 8;
+        T ca[2][2][5];
 #pragma unroll
         for (int z = 0; z < 2; ++z)
 #pragma unroll
@@ -1116,8 +1119,18 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
                 const bool has = z < nzc && y < nyc;
                 const int64_t o = ((int64_t)(zc[z] * ny + yc[y]) * NFP + split_fp<N>(jc[y], kc[z])) * ni + gi;
 #pragma unroll
-                for (int v = 0; v < 5; ++v) ca[z][y][v] = has ? (double)Fa[o * 5 + v] : 0.0;
+                for (int v = 0; v < 5; ++v) ca[z][y][v] = has ? Fa[o * 5 + v] : (T)0;
             }
+        auto sum_rows = [&]() {
+#pragma unroll
+            for (int z = 0; z < 2; ++z)
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+                    if (z < nzc && y < nyc)
+#pragma unroll
+                        for (int v = 0; v < 5; ++v) r[v] += (double)ca[z][y][v];
+        };
+        if (!PAIRS) sum_rows();
         if (xface) {
 #pragma unroll
             for (int z = 0; z < 2; ++z)
@@ -1127,17 +1140,14 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
                     if (z < nzc && y < nyc && (ex == 0 || ec % EB == 0)) {
                         const int64_t ob = ((int64_t)(ex == 0 ? ec + nx - 1 : ec - 1) * NB + split_fp<N>(jc[y], kc[z])) * 5;
 #pragma unroll
-                        for (int v = 0; v < 5; ++v) ca[z][y][v] += (double)Fb[ob + v];
+                        for (int v = 0; v < 5; ++v) {
+                            if (PAIRS) ca[z][y][v] += Fb[ob + v];
+                            else r[v] += (double)Fb[ob + v];
+                        }
                     }
                 }
         }
-#pragma unroll
-        for (int z = 0; z < 2; ++z)
-#pragma unroll
-            for (int y = 0; y < 2; ++y)
-                if (z < nzc && y < nyc)
-#pragma unroll
-                    for (int v = 0; v < 5; ++v) r[v] += ca[z][y][v];
+        if (PAIRS) sum_rows();
     } else {
         if constexpr (NIP == 0) {
             return;
@@ -1168,7 +1178,7 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
                 c1[v] = i == 0 ? Fb[o1 + v] : (T)0;
             }
 #pragma unroll
-            for (int v = 0; v < 5; ++v) r[v] = (double)c0[v] + (double)c1[v];  // absent: zero
+            for (int v = 0; v < 5; ++v) r[v] = i == 0 ? (double)c0[v] + (double)c1[v] : (double)c0[v];
         }
     }
 #pragma unroll
