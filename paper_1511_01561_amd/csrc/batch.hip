@@ -589,11 +589,17 @@ __global__ __launch_bounds__((col_threads<N, T>()), (col_blocks<N, T, MODE>())) 
 // contractions FP32, rho, 1/rho, rho'/rho and p' formed in FP64 as there);
 // the tail is the split DSS.  FP64: three workgroups per CU at N = 3, 4 (41 and
 // 50 KB of LDS; at N = 3 four would spill 48 bytes: 64x64x16 98 against 85 us),
-// four below; N = 5..8 as noted below.  Mixed: four waves per SIMD below N = 4,
-// three at N = 4 (four spill 48 bytes: step 854 against 789 us).
+// four below; N = 5..8 as noted below.  Mixed: four waves per SIMD.
 template <int N, typename T> constexpr int col2_waves()
 {
-    return sizeof(T) == 4 ? (N == 4 ? 3 : 4) : (N <= 2 ? 4 : (N <= 4 ? 3 : 2));
+    return sizeof(T) == 4 ? 4 : (N <= 2 ? 4 : (N <= 4 ? 3 : 2));
+}
+// nodes gathered together: fewer than the column where the registers of more cost
+// a wave or more (mixed N = 4, 106 for 138: 64x64x16 step 789 -> 761 us; N = 2, 79 for
+// 98: 128x128x16 528 -> 473; FP64 N = 8 1,082 -> 1,070 at 32x32x8, N = 7 210 -> 208 at 17x17x8)
+template <int N, typename T> constexpr int col2_group()
+{
+    return sizeof(T) == 8 ? (N >= 7 ? 4 : N + 1) : N == 4 ? 3 : N == 2 ? 1 : N + 1;
 }
 // doubles after each element's tile: at N = 4, 8 spread the xi and eta rows of
 // the two or three elements a wavefront spans over the LDS banks (50,640
@@ -668,7 +674,7 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
         if (gi == a.ni) gi = 0;
         if (gj == a.nj) gj = 0;
         const int base = gi + a.ni * gj, layer = a.ni * a.nj;
-        gather_column<P, P>(a, it.theta0, base, layer, be.ez * N,
+        gather_column<P, col2_group<N, T>()>(a, it.theta0, base, layer, be.ez * N,
                                              [&](int k, const double *qv, double rb, double pp) {
                                                  const int l = c + PP * k;
                                                  rho[k] = rb + qv[0];
