@@ -11,6 +11,16 @@
 #include <vector>
 
 namespace numa {
+// The mesh leaves the way its stages run to the launch's size: NUMA_STAGE_AUTO,
+// and NUMA_STAGE_SPLIT with the stored metric (a small launch takes twice as long
+// through the split DSS as with one node per lane: 51 k nodes at N = 7 89 against 39
+// us a step).
+static bool stage_by_size(const Mesh &m)
+{
+    return m.stage_mode == NUMA_STAGE_AUTO ||
+           (m.stage_mode == NUMA_STAGE_SPLIT && m.metric_mode == NUMA_METRIC_STORED);
+}
+
 namespace {
 
 using namespace dev;
@@ -1578,11 +1588,13 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
     const int eb = split ? split_eb<N>() : col ? col_eb<N, T>() : 1;
     // FP64 update that uses q_s (b != 0): the column and one-node-per-lane
     // element kernels fold q_s into the contributions (the streaming one,
-    // which runs at its register limit, does not).  The weighted sum of the fold
+    // which runs at its register limit, does not, nor what a small launch of its
+    // orders runs in its place).  The weighted sum of the fold
     // rounds q_s once per copy (against 64-bit evaluation, N = 2: 1.4e-16 where
     // the update alone leaves 7.3e-17).  With the stored metric, on x extents
     // that numa_step_batch does not take (one item), the finish reads q_s instead.
-    B.fold = std::is_same<T, double>::value && B.cb != 0.0 && (split || !(col && kind == 1)) &&
+    B.fold = std::is_same<T, double>::value && B.cb != 0.0 &&
+             (split || !(recompute && kind == 1 && !stage_by_size(*items[0].mesh))) &&
              (recompute || box_batchable(*items[0].mesh));
     int64_t eo = 0, bo = 0;
     for (int k = 0; k < n; ++k) {
@@ -1885,16 +1897,6 @@ int32_t run_filter_split(const Mesh &m, const double *F, double *q, hipStream_t 
 
 }  // namespace
 
-// The mesh leaves the way its stages run to the launch's size: NUMA_STAGE_AUTO,
-// and NUMA_STAGE_SPLIT with the stored metric (a small launch takes twice as long
-// through the split DSS as with one node per lane: 51 k nodes at N = 7 89 against 39
-// us a step).
-static bool stage_by_size(const Mesh &m)
-{
-    return m.stage_mode == NUMA_STAGE_AUTO ||
-           (m.stage_mode == NUMA_STAGE_SPLIT && m.metric_mode == NUMA_METRIC_STORED);
-}
-
 bool filter_split_ok(const Mesh &m)
 {
     // few nodes: one per lane and the gather finish, whose chains are shorter
@@ -1982,6 +1984,15 @@ int auto_route_stored(int N, int32_t prec, int64_t nl)
     return prec == NUMA_PREC_MIXED || nl < node64[N] ? kNode : kSplit;
 }
 
+// A mesh whose schedule is named: the split DSS where it applies, else the gather;
+// x extents that no batch takes with one node per lane while the default does (N = 8
+// mixed, 73 k nodes: 41 against 60 us a step through the streaming kernel).
+static int named_route(const Mesh &m, int32_t prec)
+{
+    if (split_ok(m, prec)) return kSplit;
+    return box_batchable(m) || auto_route(m.N, prec, m.nl) != kNode ? kGather : kNode;
+}
+
 int32_t launch_batch_stage(const StepItem *items, int n, int32_t prec, int phase, hipStream_t s)
 {
     // items the fused block kernels take (pencil.hip), the colour passes, the
@@ -2000,7 +2011,7 @@ int32_t launch_batch_stage(const StepItem *items, int n, int32_t prec, int phase
             const Mesh &m = *items[k].mesh;
             const int g = pencil_stage_ok(items[k], prec)       ? 4
                           : colour_ok(m)                        ? kColour
-                          : !stage_by_size(m)                   ? (split_ok(m, prec) ? kSplit : kGather)
+                          : !stage_by_size(m)                   ? named_route(m, prec)
                           : m.metric_mode == NUMA_METRIC_STORED ? auto_route_stored(m.N, prec, nl)
                                                                 : auto_route(m.N, prec, nl);
             part[g][cnt[g]++] = items[k];
