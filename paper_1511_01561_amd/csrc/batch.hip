@@ -1707,20 +1707,37 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
     return NUMA_OK;
 }
 
-// The finish segment of a launch: the widest of three whose last segment
+// The finish segment of a launch.  N = 3: the widest of three whose last segment
 // leaves at most a quarter of a row's lanes idle on every item, else the
-// narrowest.  At N = 3 a 4-element segment is 12 lattice points, 96 of every
-// 128 bytes of a state line; 16 elements are 48 points, three whole lines
-// (measured at 64x64x16: finish 82 -> 61 us); at N = 1, 2 the narrow segment
-// fills 4 and 32 lanes of a wavefront.  The per-node code and its order of the
-// copies do not depend on the segment: results are the same bit for bit
-// whichever segment a launch takes.
+// narrowest; a 4-element segment is 12 lattice points, 96 of every 128 bytes of a
+// state line, 16 elements are 48 points, three whole lines (measured at 64x64x16:
+// finish 82 -> 61 us).  N = 1, 2: the one that launches fewest lanes, whole
+// wavefronts counted (segments of 4 and 16 elements fill 4 and 16 lanes of one at
+// N = 1), the wider of equals.  The per-node code and its order of the copies do
+// not depend on the segment: results are the same bit for bit whichever
+// segment a launch takes.
 template <int N> constexpr int seg_wide() { return N == 1 ? 64 : N <= 3 ? 16 : seg_for<N>(); }
 template <int N> constexpr int seg_mid() { return N == 1 ? 16 : N <= 3 ? 8 : seg_for<N>(); }
 
 template <int N>
 int pick_seg(const StepItem *items, int n)
 {
+    if constexpr (N <= 2) {
+        int best = 0;
+        int64_t fewest = 0;
+        for (const int seg : {seg_wide<N>(), seg_mid<N>(), seg_for<N>()}) {
+            int64_t lanes = 0;
+            for (int k = 0; k < n; ++k) {
+                const int32_t *ne = items[k].mesh->d.ne;
+                lanes += (int64_t)((ne[0] + seg - 1) / seg) * ne[1] * ne[2] * ((seg * N * N * N + 63) / 64 * 64);
+            }
+            if (!best || lanes < fewest) {
+                best = seg;
+                fewest = lanes;
+            }
+        }
+        return best;
+    }
     for (const int seg : {seg_wide<N>(), seg_mid<N>()}) {
         bool ok = true;
         for (int k = 0; k < n; ++k) {
