@@ -1963,41 +1963,57 @@ bool split_ok(const Mesh &m, int32_t prec)
 // multiply-adds per lane (N = 4: 13 us for one workgroup alone, 4.5 us with one
 // node per lane), which a large launch hides behind other workgroups and a
 // small one does not; the split DSS moves fewest bytes and has the longer chain
-// of the two column kernels.  Measured at the lines, us per step, recomputed
-// metric (N: nodes, the routes' times):
-//   FP64 node / gather / split: 1: 25 k 30 / 30 / 45, 524 k 148 / 73 / 74, 1.05 M
-//   272 / 118 / 116; 2: 83 k 34 / 35 / 50, 1.8 M 228 / 156 / 162, 3.5 M 450 /
-//   318 / 284; 3: 197 k 44 / 43 / 51, 524 k 76 / 69 / 73, 604 k - / 90 /
-//   89, 786 k 100 / 94 / 90;
-//   FP64 node / split: 4: 512 k 82 / 86, 1.02 M 127 / 130, 1.28 M 154 / 141; 5: 885 k
-//   124 / 145, 1.8 M 217 / 225, 2.7 M 346 / 315; 6: 527 k 118 / 125, 615 k 135 / 128;
-//   7: 655 k 120 / 134, 786 k 135 / 139, 1.05 M 153 / 149; 8: 560 k 131 / 153, 746 k
-//   169 / 162; at 64 elements, N = 1..8: 25-51 / 28-58 / 43-100.
-//   Mixed node / gather: 3: 131 k 34 / 37, 197 k 38 / 38; 4: 256 k 48 / 48, 384 k 58 /
-//   60, 512 k 66 / 64; 5: 442 k 66 / 69, 885 k 104 / 107, 1.3 M 141 / 135; 6: 351 k
-//   65 / 71, 527 k 85 / 84; 7: 1.05 M 122 / 134, 2.1 M 223 / 228, 2.6 M 314 / 302;
-//   8: 746 k 113 / 122, 1.5 M 189 / 202, 3.0 M 416 / 377.
+// of the two column kernels.  Its workgroups take the GPU in rounds, and a round
+// barely begun costs a whole one (N = 7, node / split us per step: 1.05 M nodes, the
+// first round full, 158 / 150; 1.18 M 177 / 205).  At N = 4..7, where the two
+// meet within the first rounds, a launch that fills its last round takes the
+// split below the line too.  Measured on 330 boxes of 2 to 192 elements a side,
+// regular and odd: the route taken is 0.4 % from the fastest in the mean.  us per
+// step about the lines (medians where several boxes have the size), recomputed metric:
+//   FP64 node / gather / split: 1: 28 k 32 / 32 / 46, 36 k 35 / 34 / 45, 1.05 M 264 /
+//   115 / 117; 2: 95 k 37 / 38 / 50, 124 k 41 / 40 / 51, 2.6 M 313 / 203 / 211, 3.5 M
+//   452 / 297 / 270; 3: 200 k 44 / 45 / 53, 576 k 81 / 83 / 84, 700 k 91 / 88 / 86;
+//   FP64 node / split: 4: 745 k 102 / 105, 895 k (full) 114 / 105, 1.04 M 128 / 130, 1.13 M
+//   137 / 132; 5: 800 k 118 / 138, 1.6 M 201 / 210, 1.9 M 232 / 226; 6: 175 k 51 / 85,
+//   345 k 94 / 90, 480 k 110 / 115, 620 k 130 / 119; 7: 1.64 M 228 / 244, 1.8 M 266 / 266,
+//   2.05 M 301 / 265; 8: 1.6 M 304 / 332, 2.0 M 400 / 398, 3.0 M 628 / 566.
+//   Mixed node / gather: 1: 28 k 29 / 31, 49 k 33 / 31; 2: 95 k 36 / 37, 124 k 39 / 38; 3:
+//   202 k 43 / 44, 262 k 48 / 46; 4: 500 k 67 / 68, 590 k 77 / 75; 5: 1.4 M 148 / 149, 1.6 M
+//   170 / 169; 6: 720 k 104 / 108, 1.1 M 141 / 139; 7: 2.1 M 233 / 237, 2.3 M 291 / 284; 8:
+//   2.3 M 300 / 304, 3.0 M 398 / 388.
+static bool split_fills(int N, int64_t nl)
+{
+    // workgroups of a round (N = 6: of its first half, one to a CU) and the part of
+    // them, in per cent, from which the last round counts as full
+    static const int run[9] = {0, 0, 0, 0, 10, 7, 5, 4, 0}, slots[9] = {0, 0, 0, 0, 768, 512, 256, 512, 0};
+    static const int part[9] = {0, 0, 0, 0, 88, 88, 75, 88, 0};
+    if (!slots[N]) return false;
+    const int64_t per = (int64_t)run[N] * (N + 1) * (N + 1) * (N + 1);
+    const int64_t wg = (nl + per - 1) / per, rounds = (wg + slots[N] - 1) / slots[N];
+    return 100 * wg >= part[N] * slots[N] * rounds;
+}
+
 int auto_route(int N, int32_t prec, int64_t nl)
 {
     //                                     N = 1      2       3        4        5       6        7        8
-    static const int64_t node64[9] = {0, 28000, 95000, 200000, 600000, 1500000, 500000, 720000, 600000};
-    static const int64_t gather64[4] = {0, 800000, 2300000, 560000};
-    static const int64_t nodemx[9] = {0, 28000, 90000, 190000, 400000, 1000000, 450000, 2300000, 1800000};
+    static const int64_t node64[9] = {0, 30000, 100000, 200000, 1100000, 1800000, 540000, 1800000, 2000000};
+    static const int64_t gather64[4] = {0, 1200000, 2800000, 600000};
+    static const int64_t nodemx[9] = {0, 35000, 110000, 240000, 520000, 1400000, 750000, 2200000, 2600000};
     if (prec == NUMA_PREC_MIXED) return nl < nodemx[N] ? kNode : kGather;
-    if (nl < node64[N]) return kNode;
+    if (nl < node64[N] && !split_fills(N, nl)) return kNode;
     return N <= 3 && nl < gather64[N] ? kGather : kSplit;
 }
 
 // With the stored metric the gather has one node per lane at every size (mixed
-// precision: always; FP64 against the split DSS).  us per step, node / split: 1:
-// 33 k 32 / 44, 131 k 55 / 45; 2: 221 k 54 / 62, 885 k 137 / 110; 3: 262 k 55 / 55,
-// 786 k 98 / 91; 4: 1.02 M 131 / 134, 1.28 M 154 / 143, 8.2 M 1,165 / 961; 5: 1.3 M
-// 172 / 181, 1.8 M 237 / 232; 6: 527 k 118 / 124, 702 k 147 / 130; 7: 655 k 120 / 134,
-// 918 k 153 / 145; 8: 560 k 134 / 156, 746 k 173 / 165.
+// precision: always; FP64 against the split DSS).  us per step, node / split: 1: 72 k
+// 43 / 45, 102 k 50 / 45; 2: 440 k 77 / 79, 1.2 M 162 / 146; 3: 576 k 84 / 93, 819 k 104 /
+// 105, 1.04 M 117 / 111; 4: 750 k 115 / 117, 900 k 123 / 109; 5: 1.6 M 238 / 263, 1.9 M
+// 310 / 300; 6: 526 k 115 / 122, 620 k 131 / 124; 7: 1.2 M 185 / 249, 1.8 M 305 / 289; 8:
+// 2.0 M 442 / 435, 3.0 M 640 / 596.
 int auto_route_stored(int N, int32_t prec, int64_t nl)
 {
     //                                     N = 1      2       3        4        5       6        7        8
-    static const int64_t node64[9] = {0, 80000, 300000, 280000, 600000, 1300000, 500000, 720000, 600000};
+    static const int64_t node64[9] = {0, 85000, 650000, 850000, 800000, 1700000, 590000, 1700000, 2000000};
     return prec == NUMA_PREC_MIXED || nl < node64[N] ? kNode : kSplit;
 }
 
