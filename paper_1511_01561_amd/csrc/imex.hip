@@ -275,8 +275,8 @@ __device__ __forceinline__ double gat(double w0, double wN, int e, int k, double
     return dk / hk;
 }
 
-// One step's vertical correction of lines too tall for k_imex_lines (below):
-// one lane per line, four passes along it;
+// One step's vertical correction of the lines that k_imex_lines (below) does not
+// take: one lane per line, four passes along it;
 // an element's N+1 nodes at a time, node e N + N finishing with element e + 1
 // (or as the top wall node).
 template <int N, bool SHELL>
@@ -464,9 +464,10 @@ __global__ __launch_bounds__(256) void k_imex_solve(ImexArgs a)
 // of 8 bytes fill a 128-byte cache line.  Element derivatives meet at the
 // layer interfaces through LDS; the right side of the band system and its
 // solution stay in LDS (X), the line's other values in the lanes' registers, so
-// that every state value, reference value and factor is read once.  Per unique
-// node (box) 34 doubles are read and 10 written, so the kernel is bound by
-// memory: 32x32x16, N = 4 (1.06 M nodes, 16,384 lines, 375 MB) 372 -> 84 us,
+// that values are read once but for theta' of both levels (and where imex_keeps
+// says so rho' and w) on the box, and q* on the shell, which come from the caches
+// again.  Per unique node (box) 34 doubles are read and 10 written, so the kernel
+// is bound by memory: 32x32x16, N = 4 (1.06 M nodes, 16,384 lines, 375 MB) 372 -> 84 us,
 // 4.5 TB/s, against one lane per line over the whole kernel (k_imex_solve:
 // 64 workgroups there, each value's loads behind the level before it).
 constexpr int kLines = 16;
@@ -475,7 +476,7 @@ constexpr int kChunk = 8;  // levels of factors staged in LDS at a time
 template <int N>
 constexpr int solve_stage() { return kChunk * (2 * N + 1) * kLines; }
 
-inline int imex_pad_levels(int nk) { return (nk + kChunk - 1) / kChunk * kChunk; }
+__host__ __device__ inline int imex_pad_levels(int nk) { return (nk + kChunk - 1) / kChunk * kChunk; }
 
 // LDS of k_imex_lines: X, three interface exchanges, the staged factors
 template <int N>
@@ -560,7 +561,8 @@ __device__ __forceinline__ void band_solve(const double *lu, int64_t nh, int64_t
     }
 }
 
-// D f on one element's nodes (the zeta derivative)
+// D f on one element's nodes (the zeta derivative), once per phase: D from the
+// kernel arguments (dloc's callers loop over elements)
 template <int N>
 __device__ __forceinline__ void derive(const ImexArgs &a, const double (&f)[N + 1], double (&df)[N + 1])
 {
@@ -589,7 +591,7 @@ __global__ __launch_bounds__(MAXT) void k_imex_lines(ImexArgs a)
 {
     constexpr int P = N + 1;
     extern __shared__ double sm[];
-    const int nk = a.nk, nz = (nk - 1) / N, nkp = (nk + kChunk - 1) / kChunk * kChunk;
+    const int nk = a.nk, nz = (nk - 1) / N, nkp = imex_pad_levels(nk);
     double *X = sm, *E0 = X + nkp * kLines, *E1 = E0 + nz * kLines, *E2 = E1 + nz * kLines, *F = E2 + nz * kLines;
     const int t = threadIdx.x, line = t % kLines, e = t / kLines;
     const int64_t nh = a.nh, nu = a.nu;
@@ -794,19 +796,29 @@ ImexArgs imex_args(Mesh &m, double dt, double ra, double *qprev, double *qcur)
     return a;
 }
 
-// A lane per (line, element layer): up to 32 layers, 512 lanes, the most that
-// leaves a lane 256 registers (N = 5, 20 layers at 32x32: step 897 -> 588 us,
-// N = 6, 24 layers at 16x16: 1,079 -> 362 us); taller lines keep one lane per
-// line.
+// A lane per (line, element layer) up to 32 layers, 512 lanes, the most that
+// leaves a lane 256 registers.  Above 16 layers N >= 6 spills (box 372, 292, 772
+// bytes a lane at N = 6, 7, 8, shell N = 5..8 156, 384, 608, 820) and still gains
+// (step, one lane per line / per line and layer, us): box N = 5 16x16x24 662 / 179,
+// N = 6 1,046 / 340, N = 7 16x16x17 1,154 / 468, N = 8 1,747 / 926; shell N = 5 6x8x8x24
+// 1,275 / 347, N = 6 2,102 / 662, N = 7 6x8x8x17 1,671 / 968, N = 8 2,497 / 2,055.  Taller
+// lines keep one lane per line, and so do many lines of a single layer, where a
+// quarter of the wavefront's lanes have one (nz = 1: box N = 5 57,600 lines 68 / 77, N = 7
+// 50,176 99 / 120, shell N = 4 55,296 68 / 78; N = 3 31,104 43 / 41, N = 7 28,224 89 / 75).
 template <int N>
-bool imex_lines_ok(int nk) { return (nk - 1) / N * kLines <= 512 && imex_lines_lds<N>(nk) <= 65536; }
+bool imex_lines_ok(int nk, int64_t nh)
+{
+    const int nz = (nk - 1) / N;
+    if (nz == 1 && N >= 4 && nh >= 33000) return false;
+    return nz * kLines <= 512 && imex_lines_lds<N>(nk) <= 65536;
+}
 
 template <int N>
 int32_t launch_imex_n(const ImexArgs &a, bool factor, size_t lds, hipStream_t s)
 {
     if (factor)
         hipLaunchKernelGGL((k_imex_factor<N>), dim3((unsigned)a.nh), dim3(64), lds, s, a);
-    else if (imex_lines_ok<N>(a.nk)) {
+    else if (imex_lines_ok<N>(a.nk, a.nh)) {
         const int nz = (a.nk - 1) / N, bt = nz < 4 ? 64 : (nz * kLines + 63) / 64 * 64;
         const dim3 grid((unsigned)((a.nh + kLines - 1) / kLines)), block(bt);
         const size_t ldsl = imex_lines_lds<N>(a.nk);
