@@ -62,7 +62,7 @@ struct Batch {
     double ca, cb;  // weights of the reference state and of the stage in the update (same for all items)
     double gamma, g0;
     const void *D;
-    const double *xi, *w, *Dd;  // FP64 GLL nodes, weights, derivative matrix
+    const double *xi, *w;  // FP64 GLL nodes, weights
     double eos[kEosTerms];
     BatchItem it[kMaxBatch];
 };
@@ -143,7 +143,6 @@ __device__ __forceinline__ RhsArgs<T> elem_args(const Batch &B, const BatchItem 
     for (int c = 0; c < kEosTerms; ++c) a.eos[c] = B.eos[c];
     a.xi = B.xi;
     a.w = B.w;
-    a.Dd = B.Dd;
     return a;
 }
 
@@ -611,14 +610,14 @@ template <int N, typename T> constexpr int col2_group()
 {
     return sizeof(T) == 8 ? (N >= 7 ? 4 : N + 1) : N == 4 ? 3 : N == 2 ? 1 : N + 1;
 }
-// doubles after each element's tile: at N = 4, 8 spread the xi and eta rows of
+// doubles after each element's tile: eight at N = 4 spread the xi and eta rows of
 // the two or three elements a wavefront spans over the LDS banks (50,640
 // bytes, still three workgroups per CU)
 template <int N, typename T = double> constexpr int col2_pad() { return sizeof(T) == 8 && N == 4 ? 8 : 0; }
 // N = 5, 6 (seven and five elements per 256-lane workgroup, 60 and 69 KB of
 // LDS): two waves per SIMD
 //
-// STORED: the metric is read instead of recomputed: the four entries of it
+// STORED (N = 8 spills 32 bytes a lane): the metric is read instead of recomputed: the four entries of it
 // that vary on a box (zeta_x, zeta_y, zeta_z, J w), a node ahead of its use in
 // the first pass, J w and the others again (from the caches) in the second.
 template <int N, typename T = double, bool STORED = false>
@@ -1205,8 +1204,6 @@ __global__ __launch_bounds__(256) void k_fin_split(Batch B)
         for (int v = 0; v < 5; ++v) o[v] = rk_update_folded(sc, qnv[v], r[v]);
     } else {
         PointArgs p;
-        p.off = nullptr;
-        p.idx = nullptr;
         p.Minv = it.Minv;
         p.nrm = it.nrm;
         p.nl = 0;
@@ -1261,8 +1258,6 @@ __global__ void k_colour_finish(Batch B)
         return;
     }
     PointArgs p;
-    p.off = nullptr;
-    p.idx = nullptr;
     p.Minv = it.Minv;
     p.nrm = it.nrm;
     p.nl = 0;
@@ -1527,8 +1522,6 @@ __global__ void k_fin_batch(Batch B)
     const uint32_t ez = fdiv(t, it.fy);
     const int ey = (int)(t - ez * it.fy.d);
     PointArgs p;
-    p.off = nullptr;
-    p.idx = nullptr;
     p.Minv = it.Minv;
     p.nrm = it.nrm;
     p.nl = 0;
@@ -1575,7 +1568,6 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
     B.D = std::is_same<T, float>::value ? (const void *)items[0].mesh->dv.D32 : (const void *)items[0].mesh->dv.D64;
     B.xi = items[0].mesh->dv.xi64;
     B.w = items[0].mesh->dv.w64;
-    B.Dd = items[0].mesh->dv.D64;
     eos_coeffs(B.gamma, B.eos);
     // the recomputed metric runs a column kernel, EB elements per workgroup:
     // registers for every field's column up to N = 4, the streaming variant

@@ -160,7 +160,7 @@ struct RhsArgs {
     const int32_t *shid;        // shell, recomputed metric: horizontal unique id of each column
     int64_t nh;                 // shell: horizontal nodes
     FastDiv feh;                // shell: division by the elements of one layer (6 ne^2)
-    const double *xi, *w, *Dd;  // FP64 GLL nodes, weights, derivative matrix
+    const double *xi, *w;  // FP64 GLL nodes, weights
     BoxMetric bm;               // box: constants of the recomputed metric
     double eos[kEosTerms];      // coefficients of the binomial series of (1 + x)^gamma - 1
     double cdt;                 // shell stage (fold != 0): the stage's cdt
@@ -466,7 +466,6 @@ __device__ __forceinline__ bool element_rhs(const RhsArgs<T> &a, int64_t e, int 
 }
 
 struct PointArgs {
-    const int32_t *off, *idx;
     const double *Minv, *nrm;
     int64_t nl, nu, nh;
     int walls;
@@ -484,8 +483,6 @@ inline const double *stage_minv(const Mesh &m)
 inline PointArgs point_args(const Mesh &m)
 {
     PointArgs p;
-    p.off = m.dv.off;
-    p.idx = m.dv.idx;
     p.Minv = m.dv.Minv;
     p.nrm = m.dv.nrm;
     p.nl = m.nl;

@@ -113,8 +113,6 @@ __device__ __forceinline__ void pen_finish(const PenItem &it, const PenBatch &B,
         return;
     }
     PointArgs p;
-    p.off = nullptr;
-    p.idx = nullptr;
     p.Minv = it.Minv;
     p.nrm = it.nrm;
     p.nl = 0;

@@ -137,7 +137,7 @@ template <int N, typename T> constexpr int64_t shell_col_from()
 // elements) FP64 304 -> 234 us, mixed 221 -> 155; N = 2 83 -> 37; 20x20x8 at N = 5
 // 215 -> 137, mixed 133 -> 93; 16x16x8 at N = 6 273 -> 170, mixed 191 -> 101; 14x14x8
 // at N = 7 299 -> 205; mixed 12x12x8 at N = 8 255 -> 157.  Waves per SIMD: FP64 at
-// N = 4 three spill 128 bytes (282 against 234 us).
+// N = 4 three spill 128 bytes (282 against 234 us); N = 7 spills 32 at two.
 template <int N, typename T>
 __global__ __launch_bounds__((shell_threads<N, T>()), (shell_waves<N, T>())) void k_shell_col(RhsArgs<T> a, int ne, T *out)
 {
@@ -372,7 +372,6 @@ void launch_t(Mesh &m, const T *met, const T *D, const double *q, TO *out, bool 
     eos_coeffs(m.gamma, a.eos);
     a.xi = m.dv.xi64;
     a.w = m.dv.w64;
-    a.Dd = m.dv.D64;
     a.ni = (int)m.ni;
     a.nj = (int)m.nj;
     a.nk = m.d.periodic[2] ? (int)m.nk : -1;  // only a periodic z wraps
