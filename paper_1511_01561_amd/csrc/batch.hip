@@ -226,8 +226,6 @@ constexpr int col_eb()
 }
 template <int N, typename T>
 constexpr int col_threads() { return ((col_eb<N, T>() * (N + 1) * (N + 1) + 63) / 64) * 64; }
-// workgroups per CU the column kernel is compiled for: in FP32 at N = 4 the
-// tile (40 KB) lets four share a CU if the registers fit 4 waves per SIMD
 // elements per workgroup of the split DSS (the run length along x): the column
 // kernels' up to N = 4, above that as many as 256 lanes and an 80 KB tile
 // (two workgroups per CU) hold: 7, 5, 4, 2 at N = 5..8
@@ -242,6 +240,8 @@ template <int N> constexpr int split_threads() { return ((split_eb<N>() * (N + 1
 // its occupancy allows
 template <int N, typename T> constexpr int col_group() { return N == 4 && sizeof(T) == 4 ? 3 : N + 1; }
 template <int N, typename T> constexpr int stream_group() { return N <= 6 ? 4 : 5; }
+// workgroups per CU the column kernel is compiled for: in FP32 at N = 4 the
+// tile (40 KB) lets four share a CU if the registers fit 4 waves per SIMD
 template <int N, typename T, int MODE = 0>
 constexpr int col_blocks() { return (sizeof(T) == 4 && N == 4) ? 4 : 1; }
 

@@ -120,24 +120,25 @@ template <int N, typename T> constexpr int shell_threads()
 }
 // The column kernel from this many element-local nodes on: below, too few
 // workgroups with too long a chain each (one node per lane / columns, us per step,
-// at the element-local nodes before and after the line).  FP64: N = 1 12 k 36 / 38,
-// 29 k 43 / 39; 2: 41 k 33 / 40, 97 k 43 / 42; 3: 442 k 77 / 79, 786 k 116 / 107; 4:
-// 450 k 87 / 91, 864 k 139 / 128; 5: 187 k 60 / 67, 332 k 84 / 80; 6: 132 k 54 / 84,
-// 296 k 103 / 95; 7: 442 k 113 / 126, 786 k 170 / 160; 8: 2.6 M 652 / 709 (spills:
-// not taken).  Mixed: 3: 98 k 39 / 45, 325 k 59 / 61, 376 k 65 / 66, 508 k 77 / 73; 4:
-// 450 k 72 / 80, 864 k 117 / 114; 5: 778 k 116 / 117, 1.5 M 191 / 168; 6: 132 k 48 / 67, 296 k 84 / 77; 7: 1.8 M
-// 245 / 245; 8: 280 k 81 / 94, 630 k 141 / 134.
+// at sizes about the line).  FP64: N = 1 14 k 36 / 38, 28 k 43 / 39; 2: 78 k 39 / 41,
+// 159 k 55 / 47; 3: 555 k 87 / 91, 677 k 100 / 97; 4: 432 k 84 / 89, 588 k 102 / 93; 5: 187 k
+// 60 / 67, 332 k 82 / 79; 6: 154 k 56 / 83, 296 k 102 / 94; 7: 442 k 113 / 126, 786 k 167 /
+// 160; 8: 2.6 M 652 / 709 (spills: not taken).  Mixed: 1: 14 k 34 / 35, 28 k 38 / 35; 2: 41 k
+// 34 / 38, 78 k 39 / 39; 3: 276 k 56 / 57, 376 k 64 / 63; 4: 432 k 71 / 78, 588 k 86 / 83; 5:
+// 332 k 66 / 68, 648 k 97 / 94; 6: 154 k 48 / 67, 296 k 83 / 77; 7: 786 k 125 / 122; 8: 280 k
+// 81 / 94, 437 k 108 / 101.
 template <int N, typename T> constexpr int64_t shell_col_from()
 {
-    constexpr int64_t f64[9] = {0, 20000, 90000, 600000, 700000, 300000, 250000, 700000, INT64_MAX};
-    constexpr int64_t f32[9] = {0, 20000, 90000, 430000, 800000, 800000, 250000, 2000000, 500000};
+    constexpr int64_t f64[9] = {0, 20000, 90000, 600000, 560000, 300000, 250000, 700000, INT64_MAX};
+    constexpr int64_t f32[9] = {0, 20000, 90000, 350000, 560000, 600000, 250000, 700000, 400000};
     return sizeof(T) == 8 ? f64[N] : f32[N];
 }
 // Element kernel, one node per lane -> columns: 32x32x10 at N = 4 (61,440
-// elements) FP64 304 -> 234 us, mixed 221 -> 155; N = 2 83 -> 37; 20x20x8 at N = 5
-// 215 -> 137, mixed 133 -> 93; 16x16x8 at N = 6 273 -> 170, mixed 191 -> 101; 14x14x8
-// at N = 7 299 -> 205; mixed 12x12x8 at N = 8 255 -> 157.  Waves per SIMD: FP64 at
-// N = 4 three spill 128 bytes (282 against 234 us); N = 7 spills 32 at two.
+// elements) FP64 304 -> 234 us, mixed 217 -> 142; N = 2 83 -> 37, mixed 61 -> 27; 20x20x8
+// at N = 5 215 -> 137, mixed 131 -> 89; 16x16x8 at N = 6 273 -> 170, mixed 188 -> 101;
+// 14x14x8 at N = 7 299 -> 205, mixed 169 -> 123; mixed 12x12x8 at N = 8 251 -> 145.
+// Waves per SIMD: FP64 at N = 4 three spill 128 bytes (282 against 234 us); N = 7
+// spills 32 at two.
 template <int N, typename T>
 __global__ __launch_bounds__((shell_threads<N, T>()), (shell_waves<N, T>())) void k_shell_col(RhsArgs<T> a, int ne, T *out)
 {
