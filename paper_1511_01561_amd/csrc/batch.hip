@@ -804,13 +804,23 @@ __global__ __launch_bounds__((split_threads<N>()), (col2_waves<N, T>())) void k_
 // each from the slot it was stored in at the gather (p' from the lane's
 // registers).  Each operation is that of the other box kernels.
 // Rows are padded to an odd length (line lanes then fall on distinct banks).
-// Taken at N = 5, 6 (two waves per SIMD): 32x32x16 113 -> 106 us and 207 -> 186
-// us against k_elem_col2.  At N <= 4 the barriers cost what the reads save
+// Taken at N = 5, 6 (two waves per SIMD) for launches below rows_below()
+// element-local nodes: the fold reads the state again at the end, from the
+// caches while the launch fits them and from memory above.  us per step, this
+// kernel / k_elem_col2, recomputed metric: N = 5 1.9 M 226 / 232, 2.2 M 251 /
+// 260, 3.5 M 420 / 412, 14 M 1,756 / 1,652; N = 6 0.79 M 125 / 132, 2.2 M 276 /
+// 301, 3.5 M 452 / 462, 4.4 M 601 / 590, 22 M 3,111 / 2,904; stored: N = 5
+// 0.93 M 139 / 138, 1.9 M 259 / 252; N = 6 0.79 M 132 / 133, 2.2 M 363 / 375,
+// 2.9 M 509 / 517, 3.5 M 527 / 503.  At N <= 4 the barriers cost what the reads save
 // (64x64x16, N = 4: 207 against 211 us, N = 3: 90 against 85), at N = 7, 8 the
 // padded tile and the registers leave one wave per SIMD or spill (418 against
 // 301 us, 354 against 293).  Two lanes per column (half the registers, twice the
 // waves) measured 110 us at N = 5, 279 at N = 6, 503 at N = 8.
 template <int N> constexpr bool rows_ok() { return N == 5 || N == 6; }
+template <int N> constexpr int64_t rows_below(bool recompute)
+{
+    return N == 5 ? (recompute ? 2800000 : 0) : recompute ? 4000000 : 3200000;
+}
 template <int N> constexpr int row_len() { return (N + 1) | 1; }
 template <int N> constexpr int rows_slot() { return (N + 1) * (N + 1) * row_len<N>(); }
 template <int N, bool STORED>
@@ -1662,12 +1672,20 @@ int32_t run_chunk_seg(const StepItem *items, int n, int phase, hipStream_t s, in
             const dim3 grid((unsigned)(eo / eb)), block(split_threads<N>());
             if (phase == 1) {
                 hipLaunchKernelGGL((k_fin_split<N, T>), dim3((unsigned)bo), dim3(256), 0, s, B);
-            } else if constexpr (f64 && rows_ok<N>()) {
-                if (recompute)
-                    hipLaunchKernelGGL((k_elem_rows<N, false>), grid, block, 0, s, B);
-                else
-                    hipLaunchKernelGGL((k_elem_rows<N, true>), grid, block, 0, s, B);
-            } else if (recompute) {
+                NUMA_HIP(hipGetLastError());
+                return NUMA_OK;
+            }
+            if constexpr (f64 && rows_ok<N>()) {
+                if (eo * ((N + 1) * (N + 1) * (N + 1)) < rows_below<N>(recompute)) {
+                    if (recompute)
+                        hipLaunchKernelGGL((k_elem_rows<N, false>), grid, block, 0, s, B);
+                    else if constexpr (rows_below<N>(false) > 0)
+                        hipLaunchKernelGGL((k_elem_rows<N, true>), grid, block, 0, s, B);
+                    NUMA_HIP(hipGetLastError());
+                    return NUMA_OK;
+                }
+            }
+            if (recompute) {
                 hipLaunchKernelGGL((k_elem_col2<N, T>), grid, block, 0, s, B);
             } else {
                 if constexpr (f64) hipLaunchKernelGGL((k_elem_col2<N, T, true>), grid, block, 0, s, B);

@@ -2,7 +2,8 @@
 alone (auto_route, auto_route_stored: each item is below the order's line, their
 sum above it) gives each item the result of numa_step on it alone, bit for bit:
 one node per lane alone against the column gather, the streaming gather, the
-split DSS and its line kernel in the batch."""
+split DSS and its line kernel in the batch, and the split's line kernel alone
+(rows_below) against its column kernel in the batch."""
 import pytest
 
 from paper_1511_01561_amd import inputs
@@ -20,10 +21,14 @@ CASES = [
     (FP64, RECOMPUTE, 4, [(20, 13, 10), (21, 12, 9), (16, 16, 10)], 5),      # split
     (FP64, RECOMPUTE, 5, [(20, 13, 9), (21, 12, 9), (17, 14, 10)], 5),       # split, lines
     (FP64, RECOMPUTE, 6, [(12, 7, 7), (11, 7, 8), (9, 9, 8)], 3),            # split, lines
+    (FP64, RECOMPUTE, 5, [(40, 34, 8), (37, 30, 10)], 2),                    # lines alone, columns
+    (FP64, RECOMPUTE, 6, [(29, 31, 10), (32, 28, 9)], 2),                    # lines alone, columns
     (FP64, RECOMPUTE, 7, [(12, 9, 9), (11, 10, 9), (14, 8, 8)], 4),          # split
     (FP64, RECOMPUTE, 8, [(12, 8, 8), (11, 8, 9), (10, 9, 8)], 4),           # split
     (FP64, STORED, 4, [(20, 13, 9), (16, 16, 9), (24, 10, 9)], 4),           # split
     (FP64, STORED, 6, [(12, 7, 7), (8, 9, 8), (16, 6, 6)], 4),               # split, lines
+    (FP64, STORED, 5, [(20, 13, 9), (16, 16, 9), (24, 10, 10)], 4),          # split
+    (FP64, STORED, 6, [(24, 24, 8), (28, 21, 8)], 3),                        # lines alone, columns
     (MIXED, RECOMPUTE, 4, [(20, 13, 4), (12, 12, 8), (16, 9, 8)], 5),        # column gather
     (MIXED, RECOMPUTE, 6, [(12, 8, 8), (8, 11, 9), (16, 7, 7)], 4),          # streaming gather
 ]
